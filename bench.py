@@ -31,7 +31,8 @@ PEAK_FP64_TFLOPS = 78.6     # MI355X dense FP64 (vector and matrix)
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_TFLOPS = 157.3   # MI355X dense FP32 (matrix)
 CONFIG_ID = 3               # 20000 x 4096, 12 bins, B = 512
-KERNEL_SRCS = [os.path.join(ROOT, "paper_2501_12928_amd", "csrc", f) for f in ("likelihood.hip", "common.h")]
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2501_12928_amd", "csrc", f) for f in ("likelihood.hip", "like_device.h", "tile_factor.h",
+                                                                            "common.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "likelihood_n4096_B512_traffic.json")
 
 
@@ -42,7 +43,7 @@ def flops_per_theta(n: int) -> float:
 
 
 def kernel_digest() -> str:
-    """Hash of the likelihood kernel's code (its source and the header it
+    """Hash of the likelihood kernel's code (its source and the headers it
     includes) with comments and blank space removed: counters taken on a
     build stay valid across comment edits, and only then."""
     h = hashlib.sha256()

@@ -278,6 +278,7 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
         EOR_TRY(hipHostMalloc((void **)&c.h_inst, sizeof(eor::InstDesc)), "hipHostMalloc");
         EOR_TRY(hipMalloc(&c.d_inst, sizeof(eor::InstDesc)), "hipMalloc descriptor");
         EOR_TRY(hipMalloc(&c.counter, sizeof(unsigned int)), "hipMalloc counter");
+        EOR_TRY(hipMemsetAsync(c.counter, 0, sizeof(unsigned int), s), "clear counter");
         c.alloc_m = m;
         c.alloc_n = n;
         c.alloc_k = n_k;

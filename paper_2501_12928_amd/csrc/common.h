@@ -61,7 +61,7 @@ struct LikeParams {
     const InstDesc *inst;         // device [n_inst]
     const int2 *task;             // device [ntask] (instance, theta index), or NULL: (0, t)
     int64_t ntask;                // < 2^31
-    unsigned int *counter;        // next task; zeroed by the launch
+    unsigned int *counter;        // next task; zero before and after a launch
     double2 *Lw;                  // per-slot packed tiles of L
     int64_t slot_elems;           // complex entries per slot (room for 64-wide tiles)
     double2 *yw;                  // per-slot y

@@ -338,6 +338,8 @@ eor_status eor_group_create(int32_t n_inst, eor_ctx *const *insts, eor_group **o
     hipError_t e = hipMalloc(&g->d_inst, n_inst * sizeof(eor::InstDesc));
     if (e == hipSuccess) e = hipHostMalloc((void **)&g->h_inst, n_inst * sizeof(eor::InstDesc));
     if (e == hipSuccess) e = hipMalloc(&g->counter, sizeof(unsigned int));
+    if (e == hipSuccess) e = hipMemset(g->counter, 0, sizeof(unsigned int));
+    if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         eor_group_destroy(g);
         return eor::hip_status(e, "eor_group_create");
