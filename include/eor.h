@@ -126,6 +126,10 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
  *          variance; k > 0 the 1-based column whose Cholesky pivot was not
  *          positive and finite (LAPACK xPOTRF convention). logL = -inf
  *          whenever info != 0.
+ * A call (or what is left of one after whole rounds of the GPU's workgroups)
+ * with so few theta that one workgroup each would leave most of the GPU idle
+ * has the tiles of every theta spread over all workgroups; a theta's result is
+ * the same bits either way.
  * B = 0 is a no-op. Per-theta workspace is allocated on first use and kept;
  * the call is then asynchronous.
  * Errors: EOR_ERR_ARG, EOR_ERR_STATE (no precompute), EOR_ERR_OOM, EOR_ERR_HIP.
@@ -173,7 +177,7 @@ eor_status eor_set_workspace_limit(eor_ctx *ctx, size_t bytes);
 
 /*
  * Launch choices of this context's eor_loglike_batch / eor_loglike_terms
- * (execution parameters only; results do not depend on them beyond the
+ * where a theta has a workgroup of its own (execution parameters only; results do not depend on them beyond the
  * summation order of the tile updates, which is the same for all):
  *   stages          k-steps of 4 columns the panel update prefetches (2 or 4)
  *   wg_per_cu       theta in flight per compute unit (1 or 2)
@@ -205,7 +209,8 @@ eor_status eor_get_tile_size(const eor_ctx *ctx, int32_t *ts);
  * One eor_group_loglike call is one persistent launch: a fixed set of
  * resident workgroups takes (instance, theta) tasks, longest first, until all
  * are done, so small and large problems share the GPU without a tail per
- * dataset.
+ * dataset; with few theta, or a few large ones that would outlast the rest, the
+ * tiles of every theta are spread over all workgroups instead.
  *
  * eor_group_create: n_inst (1..64) contexts on one device, each precomputed
  * before every eor_group_loglike call. The group keeps pointers to the

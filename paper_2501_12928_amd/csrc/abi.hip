@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "common.h"
+#include "spread.h"
 
 namespace eor {
 
@@ -103,6 +104,7 @@ void free_problem(Context &c) {
 void free_work(Context &c) {
     free_dev(c.Lw);
     free_dev(c.yw);
+    free_dev(c.prog);
     c.slots = 0;
 }
 
@@ -138,9 +140,15 @@ eor_status ensure_work(Context &c, int64_t want) {
         double2 *Lw = nullptr, *yw = nullptr;
         hipError_t e1 = hipMalloc(&Lw, (size_t)slots * slot_tiles * eor::TS2 * sizeof(double2));
         hipError_t e2 = e1 == hipSuccess ? hipMalloc(&yw, (size_t)slots * c.n_pad * sizeof(double2)) : e1;
-        if (e1 == hipSuccess && e2 == hipSuccess) {
+        const size_t pb = (size_t)slots * (c.N + eor::SPREAD_EXTRA) * sizeof(int32_t);
+        int32_t *prog = nullptr;
+        hipError_t e3 = e2 == hipSuccess ? hipMalloc(&prog, pb) : e2;
+        if (e3 == hipSuccess) e3 = hipMemset(prog, 0, pb);
+        if (e3 == hipSuccess) e3 = hipStreamSynchronize(nullptr);
+        if (e3 == hipSuccess) {
             c.Lw = Lw;
             c.yw = yw;
+            c.prog = prog;
             c.slots = slots;
             c.slot_tiles = slot_tiles;
             c.slot_y = c.n_pad;
@@ -148,11 +156,29 @@ eor_status ensure_work(Context &c, int64_t want) {
         }
         if (Lw) (void)hipFree(Lw);
         if (yw) (void)hipFree(yw);
+        if (prog) (void)hipFree(prog);
         (void)hipGetLastError();
         if (slots == 1) break;
         slots = slots / 2;
     }
     return fail(EOR_ERR_OOM, "cannot allocate the per-theta workspace");
+}
+
+// Of a call of B theta in rounds of `round` (the resident workgroups, or the
+// slots if they are fewer), how many of the last ones to spread over all
+// workgroups: of a whole round and of what is left after whole rounds, those
+// that the estimates say are sooner done so. 32-wide tiles sum in another
+// order and are never spread.
+int64_t spread_count(const Context &c, int64_t B, int64_t round) {
+    if (c.tune.ts != eor::TS) return 0;
+    auto better = [&](int64_t n) {
+        const double lone = eor::lone_us(c.N) * (1.0 + 0.15 * std::min<double>(1.0, (double)n / c.num_cu));
+        return n > 0 && eor::spread_us(eor::spread_chain_us(c.N), n * eor::spread_work_us(c.N)) < 0.97 * lone &&
+               n * eor::n_tiles(c.N) < ((int64_t)1 << 31) - 4096;
+    };
+    if (B >= round && better(round)) return B;
+    const int64_t rest = B % round;
+    return better(rest) ? rest : 0;
 }
 
 }  // namespace
@@ -343,17 +369,6 @@ static eor_status loglike_impl(eor_ctx *ctx, int64_t B, const double *theta, dou
     const int64_t want = B < resident ? B : resident;
     eor_status st = ensure_work(c, want);
     if (st != EOR_OK) return st;
-    eor::LikeParams p;
-    std::memset(&p, 0, sizeof(p));
-    p.inst = c.d_inst;
-    p.task = nullptr;
-    p.ntask = B;
-    p.counter = c.counter;
-    p.Lw = c.Lw;
-    p.slot_elems = c.slot_tiles * eor::TS2;
-    p.yw = c.yw;
-    p.slot_y = c.slot_y;
-    p.call[0] = eor::CallDesc{theta, logL, info, terms};
     const int64_t grid = want < c.slots ? want : c.slots;
     const hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
@@ -370,8 +385,41 @@ static eor_status loglike_impl(eor_ctx *ctx, int64_t B, const double *theta, dou
     }
     e = c.order.enter(s);
     if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
-    e = eor::launch_likelihood(p, c.tune, grid, s);
-    if (e != hipSuccess) return hip_fail(e, "likelihood launch");
+    // Whole rounds of one theta per workgroup, and a call or remainder that
+    // would leave most of the GPU idle spread over all workgroups.
+    const int64_t lone = B - spread_count(c, B, grid);
+    if (lone > 0) {
+        eor::LikeParams p;
+        std::memset(&p, 0, sizeof(p));
+        p.inst = c.d_inst;
+        p.ntask = lone;
+        p.counter = c.counter;
+        p.Lw = c.Lw;
+        p.slot_elems = c.slot_tiles * eor::TS2;
+        p.yw = c.yw;
+        p.slot_y = c.slot_y;
+        p.call[0] = eor::CallDesc{theta, logL, info, terms};
+        e = eor::launch_likelihood(p, c.tune, std::min(grid, lone), s);
+        if (e != hipSuccess) return hip_fail(e, "likelihood launch");
+    }
+    for (int64_t b = lone; b < B; b += grid) {
+        const int64_t nb = std::min(grid, B - b);
+        eor::SpreadParams p;
+        std::memset(&p, 0, sizeof(p));
+        p.inst = c.d_inst;
+        p.ntask = (int32_t)nb;
+        p.n_max = (int32_t)c.N;
+        p.units = nb * eor::n_tiles(c.N);
+        p.counter = c.counter;
+        p.prog = c.prog;
+        p.Lw = c.Lw;
+        p.slot_elems = c.slot_tiles * eor::TS2;
+        p.yw = c.yw;
+        p.slot_y = c.slot_y;
+        p.call[0] = eor::CallDesc{theta + b * c.n_k, logL + b, info ? info + b : nullptr, terms ? terms + 4 * b : nullptr};
+        e = eor::launch_spread(p, c.num_cu, s);
+        if (e != hipSuccess) return hip_fail(e, "spread launch");
+    }
     e = c.order.leave(s);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
     return EOR_OK;

@@ -159,6 +159,7 @@ struct Context {
     // per-theta workspace: one slot per resident workgroup
     double2 *Lw = nullptr;
     double2 *yw = nullptr;
+    int32_t *prog = nullptr;     // progress words of spread theta, per slot; zero between launches
     int64_t slots = 0;
     int64_t slot_tiles = 0;      // tiles per slot
     int64_t slot_y = 0;          // complex entries of y per slot

@@ -64,6 +64,9 @@ __device__ inline void std2(double2 *p, double x, double y) {
     *(dv2 __attribute__((address_space(1))) *)p = dv2{x, y};
 }
 
+// |y|^2, with the rounding of one fixed sequence of operations.
+__device__ __forceinline__ double abs2(double2 y) { return fma(y.x, y.x, y.y * y.y); }
+
 // Operands of one k-step (4 consecutive columns k0..k0+3 of the panels) for
 // a factorisation tile of side S = 16 NCB.
 template <int NCB>

@@ -176,7 +176,7 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
                     if (q == 0) {
                         std2(yv + (int64_t)j * S + row, y.x, y.y);
                         sh.ys[row] = y;
-                        acc += y.x * y.x + y.y * y.y;
+                        acc += abs2(y);
                     } else if (q == 1) {
                         acc += log(sh.dg[row]);
                     }

@@ -12,11 +12,13 @@
 #include <iterator>
 #include <map>
 #include <new>
+#include <queue>
 #include <sstream>
 #include <string>
 #include <vector>
 
 #include "common.h"
+#include "spread.h"
 
 using eor::Context;
 
@@ -28,7 +30,15 @@ struct eor_group {
     eor::InstDesc *h_inst = nullptr;     // pinned staging
     int2 *d_task = nullptr;
     int64_t ntask = 0;
-    std::vector<int64_t> task_B;         // B per instance the task list was built for
+    // for theta spread over all workgroups: where each task's slot of L starts, the
+    // tasks with at least r tile rows, the tiles in all, and the two estimates
+    double2 *spread_y = nullptr;         // w and y of every task; the other arrays follow in the same allocation
+    int64_t *d_off = nullptr;
+    int32_t *d_count = nullptr;
+    int32_t *prog = nullptr;             // progress words, zero between launches
+    int64_t spread_rows = 0, spread_elems = 0, spread_units = 0;
+    double est_spread = 0.0, est_lone = 0.0;
+    std::vector<int64_t> task_B, task_N; // B and tile rows per instance the task list was built for
     unsigned int *counter = nullptr;
     double2 *Lw = nullptr;
     double2 *yw = nullptr;
@@ -42,6 +52,8 @@ struct eor_group {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     eor::LikeParams cap_params;
+    eor::SpreadParams cap_spread;
+    bool cap_is_spread = false;
     int64_t cap_grid = 0;
     int cap_stages = 0;
     int cap_tiles = 0;
@@ -110,13 +122,71 @@ eor_status ensure_work(eor_group &g, int64_t want) {
     return eor::fail_status(EOR_ERR_OOM, "cannot allocate the group workspace");
 }
 
+void free_tasks(eor_group &g) {
+    if (g.d_task) (void)hipFree(g.d_task);
+    if (g.spread_y) (void)hipFree(g.spread_y);
+    g.d_task = nullptr;
+    g.spread_y = nullptr;
+    g.task_B.clear();
+}
+
+// What spreading every theta of the task list over all workgroups needs, if
+// the estimates say that it is sooner done: few theta, or few large ones that
+// would keep one workgroup each busy long after the others are done.
+hipError_t build_spread(eor_group &g, const std::vector<int2> &tasks) {
+    const int64_t n = (int64_t)tasks.size(), N_max = g.inst[tasks[0].x]->c.N;
+    double chain = 0.0, work = 0.0;
+    const double load = 1.0 + 0.15 * std::min(1.0, (double)n / g.num_cu);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+    for (int i = 0; i < g.num_cu; ++i) busy.push(0.0);
+    std::vector<int64_t> off(n);
+    std::vector<int32_t> count(N_max + 1, 0);
+    int64_t elems = 0, units = 0;
+    g.est_lone = 0.0;
+    for (int64_t t = 0; t < n; ++t) {
+        const int64_t N = g.inst[tasks[t].x]->c.N;
+        chain = std::max(chain, eor::spread_chain_us(N));
+        work += eor::spread_work_us(N);
+        const double end = busy.top() + load * eor::lone_us(N);
+        busy.pop();
+        busy.push(end);
+        g.est_lone = std::max(g.est_lone, end);
+        off[t] = elems;
+        elems += eor::n_tiles(N) * eor::TS2;
+        units += eor::n_tiles(N);
+        ++count[N];
+    }
+    for (int64_t r = N_max; r > 0; --r) count[r - 1] += count[r];
+    g.est_spread = eor::spread_us(chain, work);
+    g.spread_rows = N_max;
+    g.spread_elems = elems;
+    g.spread_units = units;
+    if (!(g.est_spread < 0.97 * g.est_lone) || units >= ((int64_t)1 << 31) - 4096) {
+        g.est_spread = INFINITY;
+        return hipSuccess;
+    }
+    const size_t y = (size_t)n * N_max * eor::TS, prog = (size_t)n * (N_max + eor::SPREAD_EXTRA);
+    const size_t bytes = y * sizeof(double2) + n * sizeof(int64_t) + (count.size() + prog) * sizeof(int32_t);
+    hipError_t e = hipMalloc(&g.spread_y, bytes);
+    if (e != hipSuccess) return e;
+    g.d_off = (int64_t *)(g.spread_y + y);
+    g.d_count = (int32_t *)(g.d_off + n);
+    g.prog = g.d_count + count.size();
+    e = hipMemcpy(g.d_off, off.data(), n * sizeof(int64_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(g.d_count, count.data(), count.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset(g.prog, 0, prog * sizeof(int32_t));
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    return e;
+}
+
 // Task list: every theta of every instance, longest first (cost ~ N^3), so
 // that the persistent workgroups, taking tasks in order, approximate a
 // longest-processing-time schedule.
 eor_status build_tasks(eor_group &g, const int64_t *B) {
     const int n = (int)g.inst.size();
-    std::vector<int64_t> want(B, B + n);
-    if (g.d_task && want == g.task_B) return EOR_OK;
+    std::vector<int64_t> want(B, B + n), rows(n);
+    for (int i = 0; i < n; ++i) rows[i] = g.inst[i]->c.N;
+    if (g.d_task && want == g.task_B && rows == g.task_N) return EOR_OK;
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(),
@@ -130,16 +200,17 @@ eor_status build_tasks(eor_group &g, const int64_t *B) {
     // queued work may still read the current task list
     const hipError_t ed = g.order.drain();
     if (ed != hipSuccess) return eor::hip_status(ed, "hipEventSynchronize");
-    if (g.d_task) (void)hipFree(g.d_task);
-    g.d_task = nullptr;
+    free_tasks(g);
     g.ntask = (int64_t)tasks.size();
     g.task_B = want;
+    g.task_N = rows;
     drop_graph(g);
     if (tasks.empty()) return EOR_OK;
     hipError_t e = hipMalloc(&g.d_task, tasks.size() * sizeof(int2));
     if (e == hipSuccess) e = hipMemcpy(g.d_task, tasks.data(), tasks.size() * sizeof(int2), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = build_spread(g, tasks);
     if (e != hipSuccess) {
-        g.task_B.clear();
+        free_tasks(g);
         return eor::hip_status(e, "task list");
     }
     return EOR_OK;
@@ -229,6 +300,27 @@ eor::LikeParams make_params(const eor_group &g, const double *const *theta, doub
     return p;
 }
 
+eor::SpreadParams make_spread(const eor_group &g, const double *const *theta, double *const *logL,
+                              int32_t *const *info) {
+    eor::SpreadParams p;
+    std::memset(&p, 0, sizeof(p));
+    p.inst = g.d_inst;
+    p.task = g.d_task;
+    p.count = g.d_count;
+    p.ntask = (int32_t)g.ntask;
+    p.n_max = (int32_t)g.spread_rows;
+    p.units = g.spread_units;
+    p.counter = g.counter;
+    p.prog = g.prog;
+    p.Lw = g.Lw;
+    p.off = g.d_off;
+    p.yw = g.spread_y;
+    p.slot_y = g.spread_rows * eor::TS;
+    for (size_t i = 0; i < g.inst.size(); ++i)
+        p.call[i] = eor::CallDesc{theta[i], logL[i], info ? info[i] : nullptr, nullptr};
+    return p;
+}
+
 // Marks the end of a group call on s, for the group and for each instance
 // (whose A the launch reads until then).
 eor_status record_call(eor_group &g, hipStream_t s) {
@@ -239,7 +331,7 @@ eor_status record_call(eor_group &g, hipStream_t s) {
 
 // One launch of the whole group (eager or from the captured graph).
 eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta, double *const *logL,
-                     int32_t *const *info, const eor::Tuning &t, bool allow_graph, hipStream_t s) {
+                     int32_t *const *info, const eor::Tuning &t, bool allow_graph, bool allow_spread, hipStream_t s) {
     eor_status st = build_tasks(g, B);
     if (st != EOR_OK) return st;
     if (g.ntask == 0) return EOR_OK;
@@ -267,14 +359,26 @@ eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta,
     st = ensure_work(g, want);
     if (st != EOR_OK) return st;
     const int64_t grid = std::min<int64_t>(want, g.slots);
+    // Every theta spread over all workgroups, where that is sooner done and the
+    // workspace of the resident workgroups holds every theta's L (the tiles are
+    // then 64-wide: 32-wide ones sum in another order).
+    bool spread = allow_spread && std::isfinite(g.est_spread) &&
+                  g.spread_elems <= g.slots * g.slot_tiles * eor::TS2;
+    for (size_t i = 0; i < g.inst.size(); ++i)
+        spread = spread && (B[i] == 0 || g.h_inst[i].ts == eor::TS);
     const eor::LikeParams p = make_params(g, theta, logL, info);
+    const eor::SpreadParams sp = spread ? make_spread(g, theta, logL, info) : eor::SpreadParams();
+    auto launch = [&](hipStream_t st) {
+        return spread ? eor::launch_spread(sp, g.num_cu, st) : eor::launch_likelihood(p, t, grid, st);
+    };
     if (!(allow_graph && g.use_graph)) {
-        e = eor::launch_likelihood(p, t, grid, s);
+        e = launch(s);
         if (e != hipSuccess) return eor::hip_status(e, "group launch");
         return record_call(g, s);
     }
     const bool same = g.exec && g.cap_grid == grid && g.cap_stages == t.stages && g.cap_tiles == t.tiles &&
-                      std::memcmp(&g.cap_params, &p, sizeof(p)) == 0;
+                      g.cap_is_spread == spread && std::memcmp(&g.cap_params, &p, sizeof(p)) == 0 &&
+                      (!spread || std::memcmp(&g.cap_spread, &sp, sizeof(sp)) == 0);
     if (!same) {
         drop_graph(g);
         if (!g.cap_stream) {
@@ -283,7 +387,7 @@ eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta,
         }
         e = hipStreamBeginCapture(g.cap_stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return eor::hip_status(e, "hipStreamBeginCapture");
-        hipError_t el = eor::launch_likelihood(p, t, grid, g.cap_stream);
+        hipError_t el = launch(g.cap_stream);
         e = hipStreamEndCapture(g.cap_stream, &g.graph);
         if (el != hipSuccess) e = el;
         if (e == hipSuccess) e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
@@ -292,6 +396,8 @@ eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta,
             return eor::hip_status(e, "graph capture");
         }
         g.cap_params = p;
+        if (spread) g.cap_spread = sp;
+        g.cap_is_spread = spread;
         g.cap_grid = grid;
         g.cap_stages = t.stages;
         g.cap_tiles = t.tiles;
@@ -357,7 +463,7 @@ void eor_group_destroy(eor_group *g) {
     if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
     if (g->d_inst) (void)hipFree(g->d_inst);
     if (g->h_inst) (void)hipHostFree(g->h_inst);
-    if (g->d_task) (void)hipFree(g->d_task);
+    free_tasks(*g);
     if (g->counter) (void)hipFree(g->counter);
     delete g;
 }
@@ -373,7 +479,7 @@ eor_status eor_group_loglike(eor_group *g, const int64_t *B, const double *const
     hipError_t e = g->order.drain();
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) return eor::hip_status(e, "hipStreamSynchronize");
-    return run_group(*g, B, theta, logL, info, g->tune, true, (hipStream_t)stream);
+    return run_group(*g, B, theta, logL, info, g->tune, true, true, (hipStream_t)stream);
 }
 
 eor_status eor_group_set_graph(eor_group *g, int32_t enable) {
@@ -484,12 +590,12 @@ eor_status eor_autotune(eor_group *g, const int64_t *B, const double *const *the
     (void)hipEventCreate(&e1);
     eor_status st = EOR_OK;
     // one warm-up launch, then the mean of two timed ones
-    auto time_launch = [&](const int64_t *Bv, const eor::Tuning &t) {
-        st = run_group(*g, Bv, theta, outs.data(), nullptr, t, false, s);
+    auto time_launch = [&](const int64_t *Bv, const eor::Tuning &t, bool spread) {
+        st = run_group(*g, Bv, theta, outs.data(), nullptr, t, false, spread, s);
         float ms_sum = 0.f;
         for (int r = 0; r < 2 && st == EOR_OK; ++r) {
             (void)hipEventRecord(e0, s);
-            st = run_group(*g, Bv, theta, outs.data(), nullptr, t, false, s);
+            st = run_group(*g, Bv, theta, outs.data(), nullptr, t, false, spread, s);
             (void)hipEventRecord(e1, s);
             if (hipEventSynchronize(e1) != hipSuccess) st = eor::fail_status(EOR_ERR_HIP, "autotune timing");
             float ms = 0.f;
@@ -509,7 +615,7 @@ eor_status eor_autotune(eor_group *g, const int64_t *B, const double *const *the
                 t.stages = cand_stages[a];
                 t.tiles = cand_shape[b][0];
                 t.wg_per_cu = cand_shape[b][1];
-                const double ms = time_launch(B, t);
+                const double ms = time_launch(B, t, false);  // the shapes are those of one workgroup per theta
                 if (st == EOR_OK && ms < best_ms) {
                     best_ms = ms;
                     best = t;
@@ -534,7 +640,7 @@ eor_status eor_autotune(eor_group *g, const int64_t *B, const double *const *the
         const int cand_ts[2] = {64, 32};
         for (int c = 0; c < 2 && st == EOR_OK; ++c) {
             g->ts_bucket[b] = cand_ts[c];
-            ms_ts[c] = time_launch(Bsub.data(), g->tune);
+            ms_ts[c] = time_launch(Bsub.data(), g->tune, true);
         }
         if (st != EOR_OK) break;
         g->ts_bucket[b] = ms_ts[1] < ms_ts[0] ? 32 : 64;

@@ -1,0 +1,49 @@
+// Likelihood with the tiles of each theta spread over many workgroups
+// (spread.hip).
+#pragma once
+
+#include "common.h"
+
+namespace eor {
+
+// Words of one theta's progress row beside the N counts of finished tiles:
+// stop (the theta has failed), tails (diagonal tiles whose ln d is stored),
+// done (finished units).
+constexpr int SPREAD_EXTRA = 3;
+
+struct SpreadParams {
+    const InstDesc *inst;    // device [n_inst]
+    const int2 *task;        // device [ntask] (instance, theta index), largest instance first, or NULL: (0, t)
+    const int32_t *count;    // device [n_max + 1]: tasks of instances with at least that many tile rows, or NULL: ntask
+    int32_t ntask;           // theta, each with a slot of its own
+    int32_t n_max;           // tile rows of the largest instance
+    int64_t units;           // tiles in all (< 2^31)
+    unsigned int *counter;   // next unit; zero before and after a launch
+    int32_t *prog;           // [ntask][n_max + SPREAD_EXTRA]; zero before and after a launch
+    double2 *Lw;             // packed tiles of L, slot after slot
+    const int64_t *off;      // device [ntask]: first element of each slot, or NULL: slot * slot_elems
+    int64_t slot_elems;
+    double2 *yw;             // per-slot w, then y
+    int64_t slot_y;
+    CallDesc call[MAX_INST];
+};
+
+hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s);
+
+// Estimated times (us) of one launch, from which the callers choose (the
+// results are the same bits either way). Measured at n = 64 .. 4096 with 1 ..
+// 256 theta, and within 15% of that:
+//  - one workgroup takes a theta of N tile rows in 30 N + 1.5 N^2 + 0.93 N^3
+//    (200 us at n = 200, 4.7 ms at 1003, 253 ms at 4096), up to 15% more when
+//    all workgroups run;
+inline double lone_us(int64_t N) { return 30.0 * N + 1.5 * N * N + 0.93 * N * N * N; }
+//  - spread, a theta's diagonal tiles follow one another every 34 us, and its
+//    N (N + 1) / 2 tiles take the whole GPU 0.08 us each plus their products at
+//    78 TFLOP/s. The chain and the work of all theta overlap in part.
+inline double spread_chain_us(int64_t N) { return 34.0 * N; }
+inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 * 262144.0 * N * N * N / 78e6; }
+inline double spread_us(double chain, double work) {
+    return chain > work ? chain + 0.3 * work : work + 0.3 * chain;
+}
+
+}  // namespace eor

@@ -1,0 +1,370 @@
+// The likelihood of few theta: the tiles of each theta's factor dealt to all
+// workgroups of the GPU.
+//
+// likelihood.hip gives a theta to one workgroup, which fills the GPU with 256
+// of them and leaves it idle with few: one theta at n = 4096 took 255 ms on
+// one of 256 CUs. Here a unit of work is one 64 x 64 tile of one theta's L,
+// computed left-looking by a workgroup of four waves:
+//
+//   tile (i, j), i > j:  X = A_ij - sum_{k<j} L_ik L_jk^H   as k's tiles finish
+//                        L_ij = X Linv_jj^H,  w_i -= L_ij y_j
+//   tile (j, j):         D = A_jj + diag(Phi^{-1}) - sum_{k<j} L_jk L_jk^H,
+//                        Linv_jj and the pivots, y_j = Linv_jj w_j
+//
+// with the same sums in the same order as in likelihood.hip, so that a
+// theta's result does not depend on which of the two computed it.
+//
+// Order and progress. Units are numbered by tile columns counted from the
+// last one (so that theta of different sizes end together), within a column
+// diagonal tiles first, and taken from one counter. A unit needs only tiles
+// of earlier columns and of the diagonal of its own column, all of them
+// units with smaller numbers, and a unit is taken by a workgroup that is
+// already running: every wait is for a running workgroup, whose own waits go
+// to smaller numbers yet, so the smallest unfinished unit never waits and
+// all waits end, however few workgroups are resident. Row i's tiles finish in
+// order (tile (i, j) itself reads tile (i, j - 1)), so one counter per row
+// holds its progress. A workgroup publishes a tile by waiting for its stores
+// in every wave, a barrier, an agent-scope release and the row's counter
+// (the XCDs' L2 caches are not coherent by themselves); a reader polls the
+// counter and follows with an agent-scope acquire. A theta that fails sets a
+// stop word, its other units return at their next wait, and the last unit
+// of a theta clears its progress words for the next launch.
+//
+// What bounds it: with one theta the chain from one diagonal tile to the next,
+// 34 us (factor 13.7, its stores 1.5, seen and loaded 2, tile below 5.1, last
+// update and move to LDS 11.4): one theta at n = 4096 253 -> 2.4 ms, at n =
+// 2048 33.5 -> 1.1 ms, at n = 200 190 -> 130 us. With many theta the FP64
+// matrix cores and the panels' traffic (each unit streams both of its panels
+// alone): 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79 with 256
+// theta of one workgroup each, where two tiles share a panel; so full rounds
+// stay there (spread_count in abi.hip, build_spread in runtime.hip).
+#include <algorithm>
+
+#include "like_device.h"
+#include "spread.h"
+
+namespace eor {
+
+namespace {
+
+struct SpreadShared {
+    double2 Dt[TS * (TS + 1)];  // diagonal tile: D, then Linv; other tiles: Linv of their column
+    double2 wv[TS];             // w_j
+    double2 ys[TS];             // y_j
+    double dg[TS];              // pivots
+    double red[2][TS];
+    double lnphi[BIN_TABLE];
+    double invphi[BIN_TABLE];
+    unsigned unit;
+    int seen;
+    int fail;
+};
+
+typedef int32_t __attribute__((address_space(1))) gword;  // a word in global memory
+
+__device__ inline int load_word(const int32_t *p) {
+    return __hip_atomic_load((const gword *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline void store_word(int32_t *p, int v) {
+    __hip_atomic_store((gword *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Until rows i and j both have more than k finished tiles: the smaller of the
+// two counts, or -1 if the theta has failed. Called by the whole workgroup;
+// what the finished tiles' units wrote is visible afterwards.
+__device__ inline int wait_tiles(const int32_t *prog, int stop, int i, int j, int k, int slack, int *seen) {
+    if (threadIdx.x == 0) {
+        int v;
+        for (;;) {
+            const int a = load_word(prog + i), b = load_word(prog + j), s = load_word(prog + stop);
+            v = s ? -1 : min(a, b);
+            if (s || v > k) break;
+            if (slack <= 0)
+                __builtin_amdgcn_s_sleep(1);
+            else if (slack == 1)
+                __builtin_amdgcn_s_sleep(16);
+            else
+                __builtin_amdgcn_s_sleep(127);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        *seen = v;
+    }
+    __syncthreads();
+    const int v = uniform(*seen);
+    __syncthreads();  // before the next wait's store
+    return v;
+}
+
+// Every wave's stores so far become visible, then word = v.
+__device__ inline void publish(int32_t *word, int v) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        store_word(word, v);
+    }
+}
+
+constexpr int STAGES = 4;
+constexpr int COLB = TS * 16;  // one column of a tile, bytes
+
+// Accumulators of X = A - P Q^H (see tile_update): t1 += .., over the tiles
+// k0 .. k1 - 1 of both panels. The prefetch stays inside them.
+__device__ __forceinline__ void accumulate(rsrc_t P, rsrc_t Q, int k0, int k1, int voff, d4 t1[4], d4 t2[4], d4 t3[4]) {
+    const int beg = k0 * TS, end = k1 * TS;
+    Step<4> buf[STAGES];
+#pragma unroll
+    for (int s0 = 0; s0 < STAGES - 1; ++s0) {
+        load_step(buf[s0], P, Q, voff, (beg + 4 * s0) * COLB);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int c = beg;  // end > beg
+#pragma unroll 1
+    do {
+        if ((c & (ALIGN_COLS - 1)) == 0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < STAGES; ++u) {
+            const int cl = min(c + 4 * (u + STAGES - 1), end - 4);
+            load_step(buf[(u + STAGES - 1) % STAGES], P, Q, voff, cl * COLB);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_step(buf[u], t1, t2, t3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        c += 4 * STAGES;
+    } while (c < end);
+}
+
+// X of tile (i, j) in the accumulator layout; false if the theta has failed.
+__device__ __forceinline__ bool spread_update(SpreadShared &sh, const double2 *A, const double2 *L, const int32_t *prog,
+                                              int stop, int i, int j, int w, d4 xr[4], d4 xi[4]) {
+    const int lane = opaque(threadIdx.x & 63), l16 = lane & 15, q = lane >> 4;
+    const int64_t aoff = tile_index(i, j) * TS2 + 16 * w;
+    const rsrc_t Ar = make_rsrc(A + aoff, (int64_t)(TS2 - 16 * w) * 16);
+    const int voff = (q * TS + l16) * 16;
+    d4 t1[4], t3[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int so = (16 * cb + 4 * r) * A_COL_BYTES;
+            xr[cb][r] = ld1(Ar, voff, so);
+            t3[cb][r] = ld1(Ar, voff + 8, so);
+        }
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+        t1[cb] = d4{0, 0, 0, 0};
+        t3[cb] = xr[cb] - t3[cb];
+        xr[cb] = -xr[cb];  // T2
+    }
+    const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * TS2 + 16 * w, (int64_t)j * TS * COLB);
+    const rsrc_t Qr = make_rsrc(L + tile_index(j, 0) * TS2, (int64_t)j * TS * COLB);
+    bool ok = true;
+    if (j > 0) {
+        int k = 0;
+#pragma unroll 1
+        do {
+            const int v = wait_tiles(prog, stop, i, j, k, i <= j + 1 ? j - k - 1 : j - k, &sh.seen);
+            ok = v >= 0;
+            if (!ok) break;
+            const int e = min(v, j);
+            accumulate(Pr, Qr, k, e, voff, t1, xr, t3);
+            k = e;
+        } while (k < j);
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+        const d4 a = t1[cb], b = xr[cb];
+        xr[cb] = -(a + b);
+        xi[cb] = a - b - t3[cb];
+    }
+    return ok;
+}
+
+// Where the unit of diagonal tile j leaves ln d of a row: in the tile's slot of
+// L, above the blocks of Linv (columns 48 and 49, rows 0 .. 15).
+__device__ inline double *lnd_of(double2 *L, int j, int row) {
+    return (double *)(L + tile_index(j, j) * TS2 + (48 + (row >> 5)) * TS) + (row & 31);
+}
+
+// Rows and columns of the element that thread tid moves of lower block b
+// (0 .. 9, row order) of a tile of 4 x 4 blocks of 16 x 16.
+__device__ inline void lower_block(int b, int tid, int &row, int &col) {
+    const int bi = b < 1 ? 0 : b < 3 ? 1 : b < 6 ? 2 : 3, bj = b - bi * (bi + 1) / 2;
+    row = 16 * bi + (tid & 15);
+    col = 16 * bj + (tid >> 4);
+}
+
+// Two workgroups per CU: four waves of 256 registers each, and while one waits
+// for a tile the other computes.
+__global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
+    __shared__ SpreadShared sh;
+    const int w = uniform(threadIdx.x >> 6);
+    // units before the current column, and its tile rows left
+    int64_t base = 0;
+    int rem = a.n_max;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const unsigned t = atomicAdd(a.counter, 1u);
+            if (t == (unsigned)a.units + gridDim.x - 1) atomicExch(a.counter, 0u);
+            sh.unit = t;
+        }
+        __syncthreads();
+        const int64_t t = (unsigned)uniform((int)sh.unit);
+        __syncthreads();
+        if (t >= a.units) break;
+        int count;
+        for (;;) {
+            count = a.count ? uniform(a.count[rem]) : a.ntask;
+            if (t < base + (int64_t)count * rem) break;
+            base += (int64_t)count * rem;
+            --rem;
+        }
+        const int u = (int)((t - base) / count), slot = (int)(t - base - (int64_t)u * count);
+        int inst = 0;
+        int64_t bt = slot;
+        if (a.task) {
+            const int2 td = a.task[slot];
+            inst = uniform(td.x);
+            bt = uniform(td.y);
+        }
+        const InstDesc &I = a.inst[inst];
+        const CallDesc C = a.call[inst];
+        const int N = uniform(I.N), j = N - rem, i = j + u, stop = a.n_max;
+        const double2 *A = uniform_ptr(I.A);
+        double2 *L = uniform_ptr(a.Lw + (a.off ? a.off[slot] : slot * a.slot_elems)), *yv = uniform_ptr(a.yw + slot * a.slot_y);
+        int32_t *prog = uniform_ptr(a.prog + (int64_t)slot * (a.n_max + SPREAD_EXTRA));
+        d4 xr[4], xi[4];
+        if (u <= 1) __builtin_amdgcn_s_setprio(2);
+        if (u > 0) {
+            bool ok = spread_update(sh, A, L, prog, stop, i, j, w, xr, xi);
+            if (ok) ok = wait_tiles(prog, stop, j, j, j, 0, &sh.seen) >= 0;  // Linv_jj and y_j
+            if (ok) {
+                const int tid = opaque(threadIdx.x);
+                const double2 *V = L + tile_index(j, j) * TS2;
+                double2 v[10];
+#pragma unroll
+                for (int b = 0; b < 10; ++b) {
+                    int row, col;
+                    lower_block(b, tid, row, col);
+                    v[b] = ldd2(V + col * TS + row);
+                }
+                if (tid < TS) sh.ys[tid] = ldd2(yv + j * TS + tid);
+#pragma unroll
+                for (int b = 0; b < 10; ++b) {
+                    int row, col;
+                    lower_block(b, tid, row, col);
+                    sh.Dt[col * (TS + 1) + row] = v[b];
+                }
+                __syncthreads();
+                double2 *wi = yv + i * TS;
+                tile_below<TS>(sh.Dt, sh.ys, xr, xi, L + tile_index(i, j) * TS2, j == 0 ? I.dbar + i * TS : wi, wi, w);
+                publish(prog + i, j + 1);
+            }
+        } else {
+            const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+            const double *th = C.theta + bt * I.n_k;
+            const int32_t bj = I.coef_bin[j * TS + 16 * w + l16];
+            const double ivj = bj >= 0 ? 1.0 / (I.bin_scale[bj] * exp10(th[bj])) : I.coef_inv[j * TS + 16 * w + l16];
+            // the theta's check comes with its first unit, ln det Phi with its last
+            double ldp = 0.0;
+            bool ok = true;
+            if (j == 0 || j == N - 1) ldp = theta_terms(I, th, sh.lnphi, sh.invphi, tid);
+            if (j == 0 && uniform(ldp == ldp ? 1 : 0) == 0) {
+                ok = false;
+                if (tid == 0) {
+                    write_result(I, C, bt, -1, 0.0, 0.0, 0.0);
+                    store_word(prog + stop, 1);
+                }
+            }
+            if (ok) ok = spread_update(sh, A, L, prog, stop, j, j, w, xr, xi);
+            if (ok) {
+                const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+                if (tid < TS) sh.wv[tid] = ldd2(j == 0 ? I.dbar + tid : yv + j * TS + tid);
+                const int lo = q * (TS + 1) + 16 * w + l16;  // [16w + l16][q]
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool diag = cb == w && l16 == q + 4 * r;
+                        sh.Dt[lo + (16 * cb + 4 * r) * (TS + 1)] =
+                            make_double2(diag ? xr[cb][r] + ivj : xr[cb][r], xi[cb][r]);
+                    }
+                }
+                __syncthreads();
+                const int f = tile_factor<TS, 4>(sh.Dt, sh.dg, &sh.fail);
+                if (f) {
+                    ok = false;
+                    if (tid == 0) {
+                        write_result(I, C, bt, j * TS + f, 0.0, 0.0, 0.0);
+                        store_word(prog + stop, 1);
+                    }
+                }
+            }
+            if (ok) {
+                const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+                const int row = 16 * w + l16;
+                const double2 y = tile_solve<TS>(sh.Dt, sh.wv, w, l16, q);
+                if (q == 0) std2(yv + j * TS + row, y.x, y.y);
+                if (j < N - 1) {
+                    double2 *V = L + tile_index(j, j) * TS2;
+#pragma unroll
+                    for (int b = 0; b < 10; ++b) {
+                        int r, c;
+                        lower_block(b, tid, r, c);
+                        const double2 v = sh.Dt[c * (TS + 1) + r];
+                        std2(V + c * TS + r, v.x, v.y);
+                    }
+                    publish(prog + j, j + 1);
+                    // beside the chain of diagonal tiles: the column's ln d
+                    if (q == 1) *lnd_of(L, j, row) = log(sh.dg[row]);
+                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    __syncthreads();
+                    if (tid == 0) {
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                        atomicAdd(prog + a.n_max + 1, 1);
+                    }
+                } else {
+                    wait_tiles(prog, stop, a.n_max + 1, a.n_max + 1, N - 2, 0, &sh.seen);  // every ln d
+                    double acc = 0.0;
+                    if (q == 0) {
+                        for (int c = 0; c < N - 1; ++c) acc += abs2(ldd2(yv + c * TS + row));
+                        acc += abs2(y);
+                    } else if (q == 1) {
+                        for (int c = 0; c < N - 1; ++c) acc += ldg(lnd_of(L, c, row));
+                        acc += log(sh.dg[row]);
+                    }
+                    if (q < 2) sh.red[q][row] = acc;
+                    __syncthreads();
+                    if (tid < 64) {
+                        double quad, logdet;
+                        row_sums(sh.red[0][tid], sh.red[1][tid], quad, logdet);
+                        if (tid == 0) write_result(I, C, bt, 0, ldp, logdet, quad);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();  // the next unit reuses the workgroup's LDS
+        if (threadIdx.x == 0) {
+            // released, so that no store of this unit to the words can land after they are cleared
+            int32_t *done = prog + a.n_max + 2;
+            const int before = __hip_atomic_fetch_add((gword *)done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == N * (N + 1) / 2 - 1) {
+                for (int e = 0; e < a.n_max + SPREAD_EXTRA; ++e) store_word(prog + e, 0);
+            }
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s) {
+    const int64_t grid = std::min<int64_t>(p.units, 2 * (int64_t)num_cu);
+    if (grid < 1) return hipSuccess;
+    hipLaunchKernelGGL(spread_kernel, dim3((unsigned)grid), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace eor
