@@ -32,7 +32,7 @@
 #include <thread>
 #include <vector>
 
-#include "common.h"
+#include "tile_factor.h"
 
 namespace eor {
 
@@ -40,21 +40,6 @@ namespace {
 
 constexpr int OT = 64;
 constexpr int OT2 = OT * OT;
-
-__device__ inline d4 mfma64(double a, double b, d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-// Orders one wave's LDS accesses across its lanes. The hardware performs a
-// wave's LDS instructions in program order; the wave-scope release, wave
-// barrier and acquire keep the compiler from moving a lane's load of a value
-// that another lane stores (or a store that another lane's load must precede)
-// across this point. No instruction is emitted for it.
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 struct OocState {
     double logdet;    // 2 sum ln L_dd
@@ -70,43 +55,59 @@ __global__ void ooc_reset_kernel(OocState *st) {
     st->info = 0;
 }
 
-// Diagonal tile of column j: add 1/phi_d to the diagonal (d < n), set the
-// padding's diagonal to 1, and add the column's ln phi_d to ln det Phi in
-// a fixed order.
-__global__ __launch_bounds__(64) void ooc_diag_kernel(double2 *__restrict__ C0, int64_t j, int64_t n,
-                                                     const double *__restrict__ theta,
-                                                     const int32_t *__restrict__ bin_of,
-                                                     const double *__restrict__ fixed_var,
-                                                     const double *__restrict__ bin_scale, OocState *st) {
-    __shared__ double lp[OT];
-    __shared__ int bad[OT];
-    const int t = threadIdx.x;
-    const int64_t d = OT * j + t;
-    double l = 0.0;
-    int b_ = 0;
-    if (d < n) {
-        const int b = bin_of[d];
-        const double phi = b >= 0 ? bin_scale[b] * exp10(theta[b]) : fixed_var[d];
-        if (!(phi > 0.0) || !isfinite(phi)) b_ = 1;
-        else {
-            C0[t * OT + t].x += 1.0 / phi;
-            l = log(phi);
+// Diagonal tiles of a pass's columns j0 .. j1-1: add 1/phi_d to the diagonal
+// (d < n), set the padding's diagonal to 1, and add the columns' ln phi_d to
+// ln det Phi, each column by a fixed tree and the columns in order. One
+// workgroup for the whole pass, a wave per column (a launch per column took
+// 4.4 us each beside the chain of factorisations).
+constexpr int DW = 16;  // waves
+
+__global__ __launch_bounds__(64 * DW) void ooc_diag_kernel(double2 *__restrict__ C, int64_t j0, int64_t j1, int64_t N,
+                                                           int64_t n, const double *__restrict__ theta,
+                                                           const int32_t *__restrict__ bin_of,
+                                                           const double *__restrict__ fixed_var,
+                                                           const double *__restrict__ bin_scale, OocState *st) {
+    __shared__ double sum[DW];
+    __shared__ int bad[DW];
+    const int t = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double total = 0.0;
+    int anybad = 0;
+    for (int64_t jb = j0; jb < j1; jb += DW) {
+        const int64_t j = jb + wv;
+        double l = 0.0;
+        int b_ = 0;
+        if (j < j1) {
+            const int64_t d = OT * j + t;
+            double2 *e = C + ((j - j0) * N - (j * (j - 1) / 2 - j0 * (j0 - 1) / 2)) * OT2 + t * OT + t;
+            if (d < n) {
+                const int b = bin_of[d];
+                const double phi = b >= 0 ? bin_scale[b] * exp10(theta[b]) : fixed_var[d];
+                if (!(phi > 0.0) || !isfinite(phi)) b_ = 1;
+                else {
+                    e->x += 1.0 / phi;
+                    l = log(phi);
+                }
+            } else {
+                *e = make_double2(1.0, 0.0);
+            }
         }
-    } else {
-        C0[t * OT + t] = make_double2(1.0, 0.0);
-    }
-    lp[t] = l;
-    bad[t] = b_;
-    __syncthreads();
-    if (t == 0) {
-        double s = 0.0;
-        int anybad = 0;
-        for (int e = 0; e < OT; ++e) {
-            s += lp[e];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+        const bool wbad = __any(b_);
+        if (t == 0) {
+            sum[wv] = l;
+            bad[wv] = wbad ? 1 : 0;
+        }
+        __syncthreads();
+        for (int e = 0; e < DW; ++e) {
+            total += sum[e];
             anybad |= bad[e];
         }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
         if (anybad && st->info == 0) st->info = -1;
-        st->lndetphi += s;
+        st->lndetphi += total;
     }
 }
 
@@ -190,255 +191,118 @@ __global__ __launch_bounds__(256, 2) void ooc_pass_kernel(double2 *__restrict__ 
     tile_sub(C + (loc(j) + (i - j)) * OT2, w, l16, q, t1, t2, t3);
 }
 
-// Diagonal tile of column j: Cholesky in LDS, ln det, the inverse of L_jj
-// and y_j = L_jj^-1 w_j. One workgroup of PT threads, blocked on 16 x 16
-// sub-blocks so that few steps wait on a barrier:
-//  - Cholesky, right-looking over the four block columns: one wave factors
-//    the diagonal block (no workgroup barrier: a wave's LDS accesses run in
-//    program order, and wave_sync keeps the compiler to it), one thread per
-//    row solves the panel below it, and the
-//    rank-16 update of the rest runs on FP64 MFMA, one wave per 16 x 16 block;
-//  - inverse: the four diagonal blocks are inverted at once, one wave each,
-//    then the blocks below them, nearest the diagonal first, one wave per
-//    block on FP64 MFMA: V_ij = -V_ii sum_{k=j..i-1} L_ik V_kj.
+// Diagonal tile of column j: the inverse of its Cholesky factor and the pivots
+// (tile_factor), ln det, and y_j = L_jj^-1 w_j, by one workgroup. L_jj itself is
+// read by nothing. Linv is written column-major, so that the tiles below read
+// it with unit stride. Bound by the factorisation's serial chain: 17.7 us, 59.9
+// with the elimination in LDS by one wave and the inverse formed afterwards.
 constexpr int PT = 512;  // threads of the diagonal factorisation
-constexpr int PB = 16;   // sub-block size
-constexpr int NPB = OT / PB;
 
-__global__ __launch_bounds__(PT) void ooc_potrf_kernel(double2 *__restrict__ C0, double2 *__restrict__ Linv,
-                                                        double2 *__restrict__ w, double2 *__restrict__ y,
+__global__ __launch_bounds__(PT) void ooc_potrf_kernel(const double2 *__restrict__ C0, double2 *__restrict__ Linv,
+                                                        const double2 *__restrict__ w, double2 *__restrict__ y,
                                                         int64_t j, OocState *st) {
-    __shared__ double2 S[OT][OT + 1];              // C_jj, then L_jj (lower)
-    __shared__ double2 V[OT][OT + 1];              // L_jj^-1 (lower; zero above)
-    __shared__ double dinv[OT], lsq[OT];
-    __shared__ double2 yj[OT];
-    __shared__ int fail_col;
+    __shared__ double2 D[OT * (OT + 1)];
+    __shared__ double2 wj[OT];
+    __shared__ double dg[OT], red[2][OT];
+    __shared__ int fail;
     if (st->info != 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, wv = uniform(tid >> 6), l16 = tid & 15, q = (tid >> 4) & 3;
     {
-        // all of the thread's loads in flight before the first LDS store
+        // the lower triangle, and its conjugate above; all loads in flight together
         double2 v[OT2 / PT];
 #pragma unroll
         for (int u = 0; u < OT2 / PT; ++u) v[u] = C0[tid + PT * u];
 #pragma unroll
         for (int u = 0; u < OT2 / PT; ++u) {
-            const int e = tid + PT * u;
-            S[e / OT][e % OT] = v[u];
-            V[e / OT][e % OT] = make_double2(0.0, 0.0);
+            const int e = tid + PT * u, r = e / OT, c = e % OT;
+            if (c <= r) D[c * (OT + 1) + r] = v[u];
+            if (c < r) D[r * (OT + 1) + c] = make_double2(v[u].x, -v[u].y);
         }
     }
-    if (tid == 0) fail_col = 0;
-    if (tid < OT) yj[tid] = w[OT * j + tid];  // w_j, read by the solve below
+    if (tid < OT) wj[tid] = w[OT * j + tid];
     __syncthreads();
-
-    for (int kb = 0; kb < NPB; ++kb) {
-        const int b0 = PB * kb, r0 = b0 + PB;
-        // diagonal block, by wave 0: lane (r = lane / 4, s = lane % 4 + 4 u)
-        if (wv == 0) {
-            const int br = lane >> 2, bs = lane & 3;
-            for (int c = 0; c < PB; ++c) {
-                const double d = S[b0 + c][b0 + c].x;
-                if (!(d > 0.0) || !isfinite(d)) {
-                    if (lane == 0) fail_col = b0 + c + 1;
-                    break;  // uniform: every lane of the wave reads the same value
-                }
-                const double l = sqrt(d), il = 1.0 / l;
-                if (bs == 0 && br > c) {
-                    const double2 x = S[b0 + br][b0 + c];
-                    S[b0 + br][b0 + c] = make_double2(x.x * il, x.y * il);
-                }
-                if (lane == 0) S[b0 + c][b0 + c] = make_double2(l, 0.0);
-                wave_sync();  // the scaled column c, stored by lanes bs = 0, is read by every lane
-                if (br > c) {
-                    const double2 a = S[b0 + br][b0 + c];
-#pragma unroll
-                    for (int u = 0; u < PB / 4; ++u) {
-                        const int sc = bs + 4 * u;
-                        if (sc > c && sc <= br) {
-                            const double2 b = S[b0 + sc][b0 + c];
-                            const double2 x = S[b0 + br][b0 + sc];
-                            // x - a conj(b)
-                            S[b0 + br][b0 + sc] = make_double2(x.x - (a.x * b.x + a.y * b.y),
-                                                               x.y - (a.y * b.x - a.x * b.y));
-                        }
-                    }
-                }
-                wave_sync();  // column c + 1 and its pivot, updated by other lanes, are read next
-            }
-        }
-        __syncthreads();
-        if (fail_col != 0) break;  // uniform: read after the barrier
-        if (r0 < OT) {
-            // panel below: row r solves x L_kk^H = s, one thread per row
-            if (tid < OT - r0) {
-                const int r = r0 + tid;
-                double2 x[PB];
-#pragma unroll
-                for (int c = 0; c < PB; ++c) {
-                    double2 a = S[r][b0 + c];
-#pragma unroll
-                    for (int t = 0; t < c; ++t) {
-                        const double2 l = S[b0 + c][b0 + t];  // x_t conj(l)
-                        a.x -= x[t].x * l.x + x[t].y * l.y;
-                        a.y -= x[t].y * l.x - x[t].x * l.y;
-                    }
-                    const double il = 1.0 / S[b0 + c][b0 + c].x;
-                    x[c] = make_double2(a.x * il, a.y * il);
-                }
-#pragma unroll
-                for (int c = 0; c < PB; ++c) S[r][b0 + c] = x[c];
-            }
-            __syncthreads();
-            // rank-16 update of the rest, S[r][s] -= sum_t L[r][t] conj(L[s][t]), by
-            // 16 x 16 blocks (I, J), kb < J <= I, one wave each on FP64 MFMA (a
-            // diagonal block is updated whole: its upper part is never read)
-            {
-                int bi = 0, bj = 0, idx = 0;
-                for (int ii = kb + 1; ii < NPB; ++ii)
-                    for (int jj = kb + 1; jj <= ii; ++jj, ++idx)
-                        if (idx == wv) bi = ii, bj = jj;
-                if (wv < idx) {
-                    const int l16 = lane & 15, q = lane >> 4;
-                    d4 t1 = d4{0, 0, 0, 0}, t2 = d4{0, 0, 0, 0}, t3 = d4{0, 0, 0, 0};
-#pragma unroll
-                    for (int s0 = 0; s0 < PB; s0 += 4) {
-                        const double2 xv = S[PB * bi + l16][b0 + s0 + q];  // A[i][k]
-                        const double2 yv = S[PB * bj + l16][b0 + s0 + q];  // B[k][j] = conj(L[s][t]) parts
-                        t1 = mfma64(xv.x, yv.x, t1);
-                        t2 = mfma64(xv.y, yv.y, t2);
-                        t3 = mfma64(xv.x + xv.y, yv.x - yv.y, t3);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        double2 &e = S[PB * bi + q + 4 * r][PB * bj + l16];
-                        e = make_double2(e.x - (t1[r] + t2[r]), e.y - (t3[r] - t1[r] + t2[r]));
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-    if (fail_col != 0) {
-        if (tid == 0) st->info = (int32_t)(OT * j + fail_col);
+    const int f = tile_factor<OT, PT / 64>(D, dg, &fail);
+    if (f) {
+        if (tid == 0) st->info = (int32_t)(OT * j + f);
         return;
     }
-    if (tid < OT) {
-        const double l = S[tid][tid].x;
-        dinv[tid] = 1.0 / l;
-        lsq[tid] = log(l);
-    }
-    __syncthreads();
-    // inverse: diagonal blocks, wave kb on block kb, lane = column
-    if (wv < NPB && lane < PB) {
-        const int b0 = PB * wv, cc = lane;
-        V[b0 + cc][b0 + cc] = make_double2(dinv[b0 + cc], 0.0);
-        for (int r = 1; r < PB; ++r) {
-            if (r > cc) {
-                double sr = 0.0, si = 0.0;
-#pragma unroll 4
-                for (int t = cc; t < r; ++t) {
-                    const double2 a = S[b0 + r][b0 + t], b = V[b0 + t][b0 + cc];
-                    sr += a.x * b.x - a.y * b.y;
-                    si += a.x * b.y + a.y * b.x;
-                }
-                const double f = -dinv[b0 + r];
-                V[b0 + r][b0 + cc] = make_double2(sr * f, si * f);
-            }
-        }
-    }
-    __syncthreads();
-    // blocks below the diagonal, distance dd = ib - jb, one wave each on FP64
-    // MFMA: X = sum_k L_ib,k V_k,jb, then V_ib,jb = -V_ib,ib X, with X kept in
-    // the wave's accumulators (lane holds X[q + 4r][l16], which is the second
-    // operand of k-step r of the next product); complex products with three
-    // real ones: re = T1 - T2, im = T3 - T1 - T2
-    for (int dd = 1; dd < NPB; ++dd) {
-        if (wv < NPB - dd) {
-            const int jb = wv, ib = jb + dd, l16 = lane & 15, q = lane >> 4;
-            d4 t1 = d4{0, 0, 0, 0}, t2 = d4{0, 0, 0, 0}, t3 = d4{0, 0, 0, 0};
-            for (int k0 = PB * jb; k0 < PB * ib; k0 += 4) {
-                const double2 l = S[PB * ib + l16][k0 + q];  // A[i][k]
-                const double2 v = V[k0 + q][PB * jb + l16];  // B[k][j]
-                t1 = mfma64(l.x, v.x, t1);
-                t2 = mfma64(l.y, v.y, t2);
-                t3 = mfma64(l.x + l.y, v.x + v.y, t3);
-            }
-            const d4 xr = t1 - t2, xi = t3 - t1 - t2;
-            d4 u1 = d4{0, 0, 0, 0}, u2 = d4{0, 0, 0, 0}, u3 = d4{0, 0, 0, 0};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double2 a = V[PB * ib + l16][PB * ib + 4 * r + q];  // V_ii (zero above its diagonal)
-                u1 = mfma64(a.x, xr[r], u1);
-                u2 = mfma64(a.y, xi[r], u2);
-                u3 = mfma64(a.x + a.y, xr[r] + xi[r], u3);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                V[PB * ib + q + 4 * r][PB * jb + l16] = make_double2(-(u1[r] - u2[r]), -(u3[r] - u1[r] - u2[r]));
-        }
-        __syncthreads();
-    }
-    // write L_jj (zero above the diagonal) and its inverse
     for (int e = tid; e < OT2; e += PT) {
-        const int r = e / OT, c = e % OT;
-        C0[e] = c < r ? S[r][c] : (c == r ? make_double2(S[r][r].x, 0.0) : make_double2(0.0, 0.0));
-        Linv[e] = c <= r ? V[r][c] : make_double2(0.0, 0.0);
+        const int c = e / OT, r = e % OT;
+        Linv[e] = c <= r ? D[c * (OT + 1) + r] : make_double2(0.0, 0.0);
     }
-    // y_j = Linv w_j (w_j in yj since the start; every thread reads it before
-    // the rows' results replace it)
-    double sr = 0.0, si = 0.0;
-    if (tid < OT) {
-#pragma unroll 4
-        for (int t = 0; t <= tid; ++t) {
-            const double2 a = V[tid][t], b = yj[t];
-            sr += a.x * b.x - a.y * b.y;
-            si += a.x * b.y + a.y * b.x;
+    if (wv < OT / 16) {
+        const int row = 16 * wv + l16;
+        const double2 v = tile_solve<OT>(D, wj, wv, l16, q);
+        if (q == 0) {
+            y[OT * j + row] = v;
+            red[0][row] = v.x * v.x + v.y * v.y;
+        } else if (q == 1) {
+            red[1][row] = log(dg[row]);
         }
     }
     __syncthreads();
-    if (tid < OT) {
-        yj[tid] = make_double2(sr, si);
-        y[OT * j + tid] = yj[tid];
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double ld = 0.0, qd = 0.0;
-        for (int d = 0; d < OT; ++d) {
-            ld += lsq[d];
-            qd += yj[d].x * yj[d].x + yj[d].y * yj[d].y;
+    if (wv == 0) {
+        double qd = red[0][tid], ld = red[1][tid];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            qd += __shfl_xor(qd, o);
+            ld += __shfl_xor(ld, o);
         }
-        st->logdet += 2.0 * ld;
-        st->quad += qd;
+        if (tid == 0) {
+            st->logdet += ld;
+            st->quad += qd;
+        }
     }
 }
 
 // L_ij = C_i Linv^H for the tiles below the diagonal (t = blockIdx.x + 1),
-// then w_i -= L_ij y_j.
-__global__ __launch_bounds__(256, 2) void ooc_trsm_kernel(double2 *__restrict__ C, const double2 *__restrict__ Linv,
-                                                       double2 *__restrict__ w, const double2 *__restrict__ y,
-                                                       int64_t j, const OocState *st) {
+// then w_i -= L_ij y_j. Eight waves: two per 16 rows, with column blocks 0 and 3
+// or 1 and 2 (block cb needs the columns up to its own of Linv, so that the two
+// have the same work), and every load of a wave in flight before its products.
+// Bound by latency: one tile per workgroup, one round of workgroups; 10.9 us,
+// 21.1 with four waves, all of Linv and its loads inside the products.
+constexpr int BT = 512;  // threads
+
+__global__ __launch_bounds__(BT) void ooc_trsm_kernel(double2 *__restrict__ C, const double2 *__restrict__ Linv,
+                                                      double2 *__restrict__ w, const double2 *__restrict__ y,
+                                                      int64_t j, const OocState *st) {
+    __shared__ double2 part[4][16];  // w_i shares of the waves with blocks 1 and 2
     if (st->info != 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = lane & 15, q = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int wv = uniform((tid >> 6) & 3), half = uniform(tid >> 8);
     const int64_t t = (int64_t)blockIdx.x + 1;
     double2 *Ct = C + t * OT2;
-    d4 t1[4], t2[4], t3[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) t1[cb] = t2[cb] = t3[cb] = d4{0.0, 0.0, 0.0, 0.0};
-    tile_xyh(Ct, Linv, wv, l16, q, t1, t2, t3);
-    // each wave reads and writes only its own 16 rows of C_t
     const double2 *yj = y + OT * j;
+    double2 x[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) x[s] = Ct[(16 * wv + l16) * OT + 4 * s + q];
     double pr[4] = {0.0, 0.0, 0.0, 0.0}, pi[4] = {0.0, 0.0, 0.0, 0.0};
+    double2 res[2][4];
+    auto block = [&](int cb, int steps, double2 *out) {
+        d4 t1 = d4{0, 0, 0, 0}, t2 = d4{0, 0, 0, 0}, t3 = d4{0, 0, 0, 0};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = 16 * wv + q + 4 * r;
+        for (int s = 0; s < 16; ++s) {
+            if (s >= steps) break;
+            const double2 v = Linv[(4 * s + q) * OT + 16 * cb + l16];
+            t1 = mfma64(x[s].x, v.x, t1);
+            t2 = mfma64(x[s].y, v.y, t2);
+            t3 = mfma64(x[s].x + x[s].y, v.x - v.y, t3);
+        }
+        const double2 b = yj[16 * cb + l16];
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const double re = t1[cb][r] + t2[cb][r], im = t3[cb][r] - t1[cb][r] + t2[cb][r];
-            Ct[row * OT + 16 * cb + l16] = make_double2(re, im);
-            const double2 b = yj[16 * cb + l16];
+        for (int r = 0; r < 4; ++r) {
+            const double re = t1[r] + t2[r], im = t3[r] - t1[r] + t2[r];
+            out[r] = make_double2(re, im);
             pr[r] += re * b.x - im * b.y;
             pi[r] += re * b.y + im * b.x;
         }
+    };
+    if (half == 0) {
+        block(0, 4, res[0]);
+        block(3, 16, res[1]);
+    } else {
+        block(1, 8, res[0]);
+        block(2, 12, res[1]);
     }
     // sum over the 16 columns of a lane group, fixed xor tree
 #pragma unroll
@@ -449,12 +313,24 @@ __global__ __launch_bounds__(256, 2) void ooc_trsm_kernel(double2 *__restrict__ 
             pi[r] += __shfl_xor(pi[r], o);
         }
     }
-    if (l16 == 0) {
+    if (half == 1 && l16 == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wv][q + 4 * r] = make_double2(pr[r], pi[r]);
+    }
+    __syncthreads();  // both waves of the rows have read C_i, and the shares are there
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int cb = half == 0 ? 3 * h : 1 + h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Ct[(16 * wv + q + 4 * r) * OT + 16 * cb + l16] = res[h][r];
+    }
+    if (half == 0 && l16 == 0) {
         const int64_t i = j + t;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             double2 &e = w[OT * i + 16 * wv + q + 4 * r];
-            e = make_double2(e.x - pr[r], e.y - pi[r]);
+            const double2 o = part[wv][q + 4 * r];
+            e = make_double2(e.x - (pr[r] + o.x), e.y - (pi[r] + o.y));
         }
     }
 }
@@ -722,9 +598,8 @@ extern "C" eor_status eor_loglike_host(int device, int64_t n, const double *A, i
             // tile columns j0 .. j1-1 of A: one contiguous block
             e = hipMemcpyAsync(L.C.p, Ah.p + col_off(j0) * OT2, (size_t)nt * TILE_B, hipMemcpyHostToDevice, s);
             if (e != hipSuccess) break;
-            for (int64_t j = j0; j < j1; ++j)
-                hipLaunchKernelGGL(ooc_diag_kernel, dim3(1), dim3(OT), 0, s, L.C.p + (col_off(j) - col_off(j0)) * OT2,
-                                   j, n, L.theta.p, bin_d.p, fix_d.p, scale_d.p, L.st.p);
+            hipLaunchKernelGGL(ooc_diag_kernel, dim3(1), dim3(64 * DW), 0, s, L.C.p, j0, j1, N, n, L.theta.p, bin_d.p,
+                               fix_d.p, scale_d.p, L.st.p);
             // earlier tile columns, rows j0 .. N-1, in windows of W columns, each read once per pass
             const int64_t W = std::max<int64_t>(1, std::min<int64_t>(j0, cap / rows0));
             for (int64_t k0 = 0; k0 < j0; k0 += W) {
@@ -746,7 +621,7 @@ extern "C" eor_status eor_loglike_host(int device, int64_t n, const double *A, i
                 double2 *Cj = L.C.p + (col_off(j) - col_off(j0)) * OT2;
                 hipLaunchKernelGGL(ooc_potrf_kernel, dim3(1), dim3(PT), 0, s, Cj, L.Linv.p, L.w.p, L.y.p, j, L.st.p);
                 if (rows > 1)
-                    hipLaunchKernelGGL(ooc_trsm_kernel, dim3((unsigned)(rows - 1)), dim3(256), 0, s, Cj, L.Linv.p,
+                    hipLaunchKernelGGL(ooc_trsm_kernel, dim3((unsigned)(rows - 1)), dim3(BT), 0, s, Cj, L.Linv.p,
                                        L.w.p, L.y.p, j, L.st.p);
                 if (j + 1 < j1)
                     hipLaunchKernelGGL(ooc_pass_kernel, dim3((unsigned)(col_off(j1) - col_off(j + 1))), dim3(256), 0,
