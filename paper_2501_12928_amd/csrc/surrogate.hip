@@ -13,7 +13,7 @@
 // standardised by the training mean and standard deviation.
 //
 // One training step is two kernels:
-//  - mlp_kernel<CT, 8, 1, true>: one workgroup per 16 samples of one member
+//  - mlp_kernel<CT, 8 or 16, 1, true>: one workgroup per 16 samples of one member
 //    gathers its inputs, runs both hidden layers, the output, the loss and
 //    the backward pass down to dZ1 with the activations in LDS and
 //    registers (FP32 MFMA 16x16x4), writes H1^T and dZ2^T (the operands of
@@ -110,15 +110,31 @@ __host__ __device__ inline int64_t share_count(int H, int n_in) { return (int64_
 // exactly zero). In an MFMA step t, lane group q = lane / 16 supplies the
 // operand pair of reduction index 4 q + t within a group of 16, for A and
 // B alike, so that each lane loads four consecutive k with one 16-byte read.
+// In the backward pass a step has few workgroups (160 at 512 samples of five
+// members) and each is a chain of two products, two sets of erf and exp and two
+// products back; widths that fill tiles of 256 take sixteen waves, four per
+// SIMD, to cover each other's latencies: 29.6 us a step's first kernel at width
+// 256 where eight took 31.8. Staging W2 through LDS, one or four stages ahead,
+// left the two W2 products at 7.6 and 6.9 us each (twice their matrix time), and
+// eight samples' groups in flight in the update made that kernel slower (12.6
+// against 10.7 us), so neither is here. FP32 MFMA and vector instructions of
+// other waves do not overlap on this part: forward only, at a million
+// proposals, the SIMDs are 55% in MFMA and 41% in vector instructions, most of
+// them erf.
 template <int CT, int NW, int RT, bool BWD>
 __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
     static_assert(!BWD || RT == 1, "the backward pass takes 16 samples per workgroup");
+    static_assert(NW != 16 || BWD, "sixteen waves in the backward pass only");
     constexpr int FS = ST * RT;       // samples per workgroup
     constexpr int HP = 16 * CT * NW;
     constexpr int HS = HP + 4;        // LDS row stride of the hidden activations
     __shared__ __align__(16) float xs[FS * XS];
     __shared__ __align__(16) float hs[FS * HS];
-    __shared__ float fpart[NW * FS];
+    // NW = 16: waves 2 v and 2 v + 1 share the units that one of eight waves
+    // has, and the second goes on with the first one's sums
+    constexpr int NV = NW == 16 ? 8 : NW;
+    __shared__ float fpart[NV * FS];
+    __shared__ f4 fhalf[NW == 16 ? NV : 1][64];
     __shared__ float dfs[FS];
     __shared__ float r2s[FS];
     const int z = blockIdx.y, s0 = blockIdx.x * FS;
@@ -235,41 +251,80 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) fp[rt][r] = 0.0f;
+    if constexpr (NW == 16) {
+        // activations of both waves side by side, the sums one after the other
+        float w3v[CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const int o = hb + 16 * c + l16;
-        const float b = o < H ? P[a.offb2 + o] : 0.0f;
-        const float w3 = o < H ? P[a.offW3 + o] : 0.0f;
+        for (int c = 0; c < CT; ++c) {
+            const int o = hb + 16 * c + l16;
+            const float b = o < H ? P[a.offb2 + o] : 0.0f;
+            w3v[c] = o < H ? P[a.offW3 + o] : 0.0f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float zz = acc[0][c][r] + b;
+                h2[c][r] = gelu_f(zz);
+                gw[c][r] = w3v[c] * gelu_grad_f(zz);
+            }
+        }
+        if ((w & 1) == 0) {
+            f4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                for (int c = 0; c < CT; ++c) fp[0][r] += h2[c][r] * w3v[c];
+                v[r] = fp[0][r];
+            }
+            fhalf[w >> 1][lane] = v;
+        }
+        __syncthreads();
+        if ((w & 1) == 1) {
+            const f4 v = fhalf[w >> 1][lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                fp[0][r] = v[r];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) fp[0][r] += h2[c][r] * w3v[c];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int o = hb + 16 * c + l16;
+            const float b = o < H ? P[a.offb2 + o] : 0.0f;
+            const float w3 = o < H ? P[a.offW3 + o] : 0.0f;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float zz = acc[rt][c][r] + b;
+                    const float hv = gelu_f(zz);
+                    fp[rt][r] += hv * w3;
+                    if constexpr (BWD) {
+                        h2[c][r] = hv;
+                        gw[c][r] = w3 * gelu_grad_f(zz);
+                    }
+                }
+        }
+    }
+    if (NW != 16 || (w & 1) == 1) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float zz = acc[rt][c][r] + b;
-                const float hv = gelu_f(zz);
-                fp[rt][r] += hv * w3;
-                if constexpr (BWD) {
-                    h2[c][r] = hv;
-                    gw[c][r] = w3 * gelu_grad_f(zz);
-                }
+                float v = fp[rt][r];
+                v += __shfl_xor(v, 8);
+                v += __shfl_xor(v, 4);
+                v += __shfl_xor(v, 2);
+                v += __shfl_xor(v, 1);
+                if (l16 == 0) fpart[(NW == 16 ? w >> 1 : w) * FS + ST * rt + 4 * q + r] = v;
             }
     }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float v = fp[rt][r];
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 1);
-            if (l16 == 0) fpart[w * FS + ST * rt + 4 * q + r] = v;
-        }
     __syncthreads();
     if (tid < FS) {
         const int s = tid, gs = s0 + s;
         float f = fpart[s];
 #pragma unroll
-        for (int v = 1; v < NW; ++v) f += fpart[v * FS + s];
+        for (int v = 1; v < NV; ++v) f += fpart[v * FS + s];
         f += P[a.offb3];
         const bool valid = gs < a.nb;
         float res = 0.0f;
@@ -392,6 +447,8 @@ struct UpdArgs {
     int H, n_in, nb;
     int64_t PP, offb1, offW2, offb2, offW3, offb3;
     float *grad;              // [z][PP], written when set
+    float *gout;              // [z][P], the same in the packed layout, written when set
+    int64_t P;
     float *loss;              // [z], written when set
     float *params, *mom, *vel;  // Adam when params is set
     float lr, b1, b2, eps;
@@ -471,6 +528,7 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(UpdArgs a) {
             if (o < a.H && i < a.H) {
                 const int64_t e = zp + a.offW2 + (int64_t)o * a.H + i;
                 if (a.grad) a.grad[e] = sum[r];
+                if (a.gout) a.gout[(int64_t)z * a.P + (e - zp)] = sum[r];
                 if (a.params) adam_update(&a.params[e], sum[r], &a.mom[e], &a.vel[e], a.lr, a.b1, a.b2, a.eps, c1, c2);
             }
         }
@@ -503,6 +561,7 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(UpdArgs a) {
     else off = a.offb3;
     const int64_t pe = zp + off;
     if (a.grad) a.grad[pe] = g;
+    if (a.gout) a.gout[(int64_t)z * a.P + off] = g;
     if (a.params) adam_update(&a.params[pe], g, &a.mom[pe], &a.vel[pe], a.lr, a.b1, a.b2, a.eps, c1, c2);
 }
 
@@ -754,12 +813,12 @@ MlpArgs net_args(const eor_surrogate &s) {
 template <int NW, int RT, bool BWD>
 void launch_mlp(const MlpArgs &a, int CT, int members, hipStream_t st) {
     const dim3 grid((unsigned)((a.nb + ST * RT - 1) / (ST * RT)), (unsigned)members), block(64 * NW);
-    if constexpr (NW == 8) {  // widths up to 512 in tiles of 128
+    if constexpr (NW == 8) {  // widths up to 512 in tiles of 128; whole tiles of 256 by sixteen waves
         switch (CT) {
         case 1: hipLaunchKernelGGL((mlp_kernel<1, NW, RT, BWD>), grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((mlp_kernel<2, NW, RT, BWD>), grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL((mlp_kernel<1, 16, RT, BWD>), grid, dim3(1024), 0, st, a); break;
         case 3: hipLaunchKernelGGL((mlp_kernel<3, NW, RT, BWD>), grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL((mlp_kernel<4, NW, RT, BWD>), grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL((mlp_kernel<2, 16, RT, BWD>), grid, dim3(1024), 0, st, a); break;
         }
     } else {                  // widths up to 512 in tiles of 64
         switch (CT) {
@@ -782,8 +841,10 @@ void launch_forward(const MlpArgs &a, int NT, int members, hipStream_t st) {
 
 // Loss, gradient and (with cfg) the Adam step of every member on a batch of
 // nb samples described by `in` (inputs and targets; no outputs).
+// With write_grad, the gradient is kept and, where not NULL, loss (one per
+// member) and grad (packed) receive both.
 void train_step(eor_surrogate &s, MlpArgs in, int nb, const eor_train_cfg *cfg, int64_t step_add, bool write_grad,
-                hipStream_t st) {
+                float *loss, float *grad, hipStream_t st) {
     const int64_t nbp = pad16(nb);
     in.nb = nb;
     in.H1T = s.H1T;
@@ -811,7 +872,9 @@ void train_step(eor_surrogate &s, MlpArgs in, int nb, const eor_train_cfg *cfg, 
     u.offW3 = s.offW3;
     u.offb3 = s.offb3;
     u.grad = write_grad ? s.grad : nullptr;
-    u.loss = write_grad ? s.loss : nullptr;
+    u.loss = loss;
+    u.gout = grad;
+    u.P = s.P;
     if (cfg) {
         u.params = s.params;
         u.mom = s.mom;
@@ -838,7 +901,7 @@ void epoch_steps(eor_surrogate &s, const eor_train_cfg &cfg, int64_t steps, int 
     in.idxz = row;
     for (int64_t k = 0; k < steps; ++k) {
         in.idx = s.idx + k * nb;
-        train_step(s, in, nb, &cfg, k, false, st);
+        train_step(s, in, nb, &cfg, k, false, nullptr, nullptr, st);
     }
     hipLaunchKernelGGL(tick_kernel, dim3(1), dim3(1), 0, st, s.d_step, steps);
 }
@@ -1015,10 +1078,8 @@ eor_status eor_surrogate_loss_grad(eor_surrogate *s, int64_t nb, const float *x,
     in.xz = nb * s->n_in;
     in.Y = y;
     in.yz = nb;
-    train_step(*s, in, (int)nb, nullptr, 0, true, hs);
-    if (loss) e = hipMemcpyAsync(loss, s->loss, s->M * sizeof(float), hipMemcpyDeviceToDevice, hs);
-    if (e == hipSuccess && grad) e = copy_params(grad, s->P, s->grad, s->PP, *s, hipMemcpyDeviceToDevice, hs);
-    if (e == hipSuccess) e = hipGetLastError();
+    train_step(*s, in, (int)nb, nullptr, 0, true, loss, grad, hs);
+    e = hipGetLastError();
     if (e == hipSuccess) e = s->order.leave(hs);
     return e == hipSuccess ? EOR_OK : eor::hip_status(e, "eor_surrogate_loss_grad");
 }
