@@ -75,27 +75,15 @@ void free_problem(Context &c) {
     free_dev(c.A);
     free_dev(c.dbar);
     free_dev(c.scal);
-    free_dev(c.coef_bin);
-    free_dev(c.coef_inv);
-    free_dev(c.bin_scale);
-    free_dev(c.bin_count);
+    free_dev(c.d_inst);  // and the tables that follow it
     free_dev(c.invvar);
     free_dev(c.partial);
-    free_dev(c.d_inst);
     free_dev(c.counter);
     if (c.h_inst) (void)hipHostFree(c.h_inst);
     c.h_inst = nullptr;
     if (c.lowp) (void)hipFree(c.lowp);
     c.lowp = nullptr;
     c.lowp_bytes = 0;
-    if (c.h_bin) (void)hipHostFree(c.h_bin);
-    if (c.h_inv) (void)hipHostFree(c.h_inv);
-    if (c.h_scale) (void)hipHostFree(c.h_scale);
-    if (c.h_count) (void)hipHostFree(c.h_count);
-    c.h_bin = nullptr;
-    c.h_inv = nullptr;
-    c.h_scale = nullptr;
-    c.h_count = nullptr;
     c.alloc_m = c.alloc_n = 0;
     c.alloc_k = -1;
     c.ready = false;
@@ -286,23 +274,28 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
         }                                        \
     } while (0)
     if (c.alloc_n == 0) {
-        c.splits = (int)std::min<int64_t>(64, (m + 255) / 256);
+        c.splits = eor::vectors_splits(m, n, c.num_cu);
         const size_t a_bytes = (size_t)eor::n_tiles(c.N) * eor::TS2 * sizeof(double2);
         EOR_TRY(hipMalloc(&c.A, a_bytes), "hipMalloc A");
         EOR_TRY(hipMalloc(&c.dbar, c.n_pad * sizeof(double2)), "hipMalloc dbar");
         EOR_TRY(hipMalloc(&c.scal, 2 * sizeof(double)), "hipMalloc scalars");
-        EOR_TRY(hipMalloc(&c.coef_bin, c.n_pad * sizeof(int32_t)), "hipMalloc bins");
-        EOR_TRY(hipMalloc(&c.coef_inv, c.n_pad * sizeof(double)), "hipMalloc fixed");
-        EOR_TRY(hipMalloc(&c.bin_scale, nk1 * sizeof(double)), "hipMalloc scales");
-        EOR_TRY(hipMalloc(&c.bin_count, nk1 * sizeof(int32_t)), "hipMalloc counts");
         EOR_TRY(hipMalloc(&c.invvar, m * sizeof(double)), "hipMalloc invvar");
-        EOR_TRY(hipMalloc(&c.partial, (size_t)c.splits * n * sizeof(double2)), "hipMalloc partial");
-        EOR_TRY(hipHostMalloc((void **)&c.h_bin, c.n_pad * sizeof(int32_t)), "hipHostMalloc");
-        EOR_TRY(hipHostMalloc((void **)&c.h_inv, c.n_pad * sizeof(double)), "hipHostMalloc");
-        EOR_TRY(hipHostMalloc((void **)&c.h_scale, nk1 * sizeof(double)), "hipHostMalloc");
-        EOR_TRY(hipHostMalloc((void **)&c.h_count, nk1 * sizeof(int32_t)), "hipHostMalloc");
-        EOR_TRY(hipHostMalloc((void **)&c.h_inst, sizeof(eor::InstDesc)), "hipHostMalloc");
-        EOR_TRY(hipMalloc(&c.d_inst, sizeof(eor::InstDesc)), "hipMalloc descriptor");
+        EOR_TRY(hipMalloc(&c.partial, (size_t)c.splits * (n + 1) * sizeof(double2)), "hipMalloc partial");
+        // descriptor, 1/v, scales, bins and counts in one block on either side, so
+        // that one copy moves them (five took 11 us each of the stream's time)
+        const size_t inv = (sizeof(eor::InstDesc) + 15) / 16 * 16, sc = inv + c.n_pad * sizeof(double),
+                     bn = sc + nk1 * sizeof(double), ct = bn + c.n_pad * sizeof(int32_t);
+        c.tab_bytes = ct + nk1 * sizeof(int32_t);
+        EOR_TRY(hipHostMalloc((void **)&c.h_inst, c.tab_bytes), "hipHostMalloc");
+        EOR_TRY(hipMalloc((void **)&c.d_inst, c.tab_bytes), "hipMalloc tables");
+        c.h_inv = (double *)((char *)c.h_inst + inv);
+        c.h_scale = (double *)((char *)c.h_inst + sc);
+        c.h_bin = (int32_t *)((char *)c.h_inst + bn);
+        c.h_count = (int32_t *)((char *)c.h_inst + ct);
+        c.coef_inv = (double *)((char *)c.d_inst + inv);
+        c.bin_scale = (double *)((char *)c.d_inst + sc);
+        c.coef_bin = (int32_t *)((char *)c.d_inst + bn);
+        c.bin_count = (int32_t *)((char *)c.d_inst + ct);
         EOR_TRY(hipMalloc(&c.counter, sizeof(unsigned int)), "hipMalloc counter");
         EOR_TRY(hipMemsetAsync(c.counter, 0, sizeof(unsigned int), s), "clear counter");
         c.alloc_m = m;
@@ -317,13 +310,9 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
         c.h_scale[b] = scale[b];
         c.h_count[b] = cnt[b];
     }
-    EOR_TRY(hipMemcpyAsync(c.coef_bin, c.h_bin, c.n_pad * sizeof(int32_t), hipMemcpyHostToDevice, s), "copy bins");
-    EOR_TRY(hipMemcpyAsync(c.coef_inv, c.h_inv, c.n_pad * sizeof(double), hipMemcpyHostToDevice, s), "copy fixed");
-    EOR_TRY(hipMemcpyAsync(c.bin_scale, c.h_scale, nk1 * sizeof(double), hipMemcpyHostToDevice, s), "copy scales");
-    EOR_TRY(hipMemcpyAsync(c.bin_count, c.h_count, nk1 * sizeof(int32_t), hipMemcpyHostToDevice, s), "copy counts");
     *c.h_inst = eor::inst_desc(c);
     c.desc_ts = c.h_inst->ts;
-    EOR_TRY(hipMemcpyAsync(c.d_inst, c.h_inst, sizeof(eor::InstDesc), hipMemcpyHostToDevice, s), "copy descriptor");
+    EOR_TRY(hipMemcpyAsync(c.d_inst, c.h_inst, c.tab_bytes, hipMemcpyHostToDevice, s), "copy tables");
 
     const double2 *Td = (const double2 *)T;
     EOR_TRY(eor::launch_precompute_vectors(c, Td, ldT, noise_var, (const double2 *)d, c.invvar, c.partial,

@@ -139,14 +139,15 @@ struct Context {
     double *coef_inv = nullptr;  // [n_pad]: 1/v_j for fixed coefficients, else 0
     double *bin_scale = nullptr; // [n_k]
     int32_t *bin_count = nullptr;// [n_k]
-    InstDesc *d_inst = nullptr;  // device copy of this dataset's descriptor
+    InstDesc *d_inst = nullptr;  // device copy of this dataset's descriptor; the four tables above follow it
     unsigned int *counter = nullptr;
     Tuning tune;
     // precompute temporaries, kept so a repeated precompute needs no allocation
     double *invvar = nullptr;    // [m]
-    double2 *partial = nullptr;  // [splits * n]
+    double2 *partial = nullptr;  // [splits * n] of dbar, then [splits] of c and sum ln sigma^2
     int splits = 0;
-    // pinned staging of the host-side tables
+    // pinned staging of the host-side tables: one block, laid out as the device's
+    size_t tab_bytes = 0;
     int32_t *h_bin = nullptr;
     double *h_inv = nullptr;
     double *h_scale = nullptr;
@@ -189,6 +190,7 @@ hipError_t launch_precompute_fp32(const Context &c, const double2 *T, int64_t ld
                                   const double *invvar, void *scratch, hipStream_t s);
 hipError_t launch_precompute_bf16(const Context &c, const double2 *T, int64_t ldT,
                                   const double *invvar, void *scratch, int nterm, hipStream_t s);
+int vectors_splits(int64_t m, int64_t n, int num_cu);
 hipError_t launch_precompute_vectors(const Context &c, const double2 *T, int64_t ldT,
                                      const double *noise_var, const double2 *d, double *invvar,
                                      double2 *partial, int splits, hipStream_t s);

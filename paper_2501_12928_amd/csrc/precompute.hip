@@ -193,74 +193,113 @@ __global__ void herk_reduce_kernel(const double2 *__restrict__ part, int64_t til
     }
 }
 
-// invvar_s = 1 / sigma_s^2
-__global__ void invvar_kernel(const double *__restrict__ noise_var, int64_t m, double *__restrict__ invvar) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < m) invvar[s] = 1.0 / noise_var[s];
-}
-
-// Partial sums of dbar_j = sum_s conj(T_sj) d_s / sigma_s^2 over one slice of rows.
-__global__ __launch_bounds__(256) void dbar_partial_kernel(const double2 *__restrict__ T, int64_t ldT,
-                                                           int64_t m, int64_t n,
-                                                           const double2 *__restrict__ d,
-                                                           const double *__restrict__ invvar,
-                                                           int64_t rows_per_split,
-                                                           double2 *__restrict__ partial) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t split = blockIdx.y;
-    if (j >= n) return;
-    const int64_t s_lo = split * rows_per_split;
-    const int64_t s_hi = s_lo + rows_per_split < m ? s_lo + rows_per_split : m;
-    double sr = 0.0, si = 0.0;
-    for (int64_t s = s_lo; s < s_hi; ++s) {
-        const double2 t = T[s * ldT + j];
-        const double2 ds = d[s];
-        const double wv = invvar[s];
-        sr += (t.x * ds.x + t.y * ds.y) * wv;
-        si += (t.x * ds.y - t.y * ds.x) * wv;
-    }
-    partial[split * n + j] = make_double2(sr, si);
-}
-
-__global__ void dbar_reduce_kernel(const double2 *__restrict__ partial, int splits, int64_t n,
-                                   int64_t n_pad, double2 *__restrict__ dbar) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_pad) return;
+// One workgroup's share of the vectors: 64 columns of T, over one slice of
+// the rows, as partial sums of dbar_j = sum_s conj(T_sj) d_s / sigma_s^2
+// (threads: column tid % 64, every fourth row from tid / 64 on); the first
+// column block also writes 1 / sigma_s^2 and the slice's share of c and of
+// -sum ln sigma_s^2. One pass over T at the rate of memory, with the reduction
+// 258 us at 20000 x 4096 (5.1 TB/s), 67 at 8000 x 2048, 8 at 480 x 200; four
+// launches, with one thread per column of slices of 256 rows or more and one
+// workgroup for the scalars, took 314, 148 and 75.
+__global__ __launch_bounds__(256) void vectors_kernel(const double2 *__restrict__ T, int64_t ldT, int64_t m, int64_t n,
+                                                      const double *__restrict__ noise_var,
+                                                      const double2 *__restrict__ d, int64_t rows_per,
+                                                      double *__restrict__ invvar, double2 *__restrict__ partial,
+                                                      double2 *__restrict__ scal_part) {
+    __shared__ double2 red[4][64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane, split = blockIdx.y;
+    const int64_t s_lo = split * rows_per, s_hi = s_lo + rows_per < m ? s_lo + rows_per : m;
     double sr = 0.0, si = 0.0;
     if (j < n) {
-        for (int s = 0; s < splits; ++s) {
-            sr += partial[s * n + j].x;
-            si += partial[s * n + j].y;
+        int64_t s = s_lo + w;
+        for (; s + 12 < s_hi; s += 16) {  // four rows in flight
+            double2 t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = T[(s + 4 * u) * ldT + j];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double2 ds = d[s + 4 * u];
+                const double wv = 1.0 / noise_var[s + 4 * u];
+                sr += (t[u].x * ds.x + t[u].y * ds.y) * wv;
+                si += (t[u].x * ds.y - t[u].y * ds.x) * wv;
+            }
+        }
+        for (; s < s_hi; s += 4) {
+            const double2 t = T[s * ldT + j], ds = d[s];
+            const double wv = 1.0 / noise_var[s];
+            sr += (t.x * ds.x + t.y * ds.y) * wv;
+            si += (t.x * ds.y - t.y * ds.x) * wv;
         }
     }
-    dbar[j] = make_double2(sr, si);
+    red[w][lane] = make_double2(sr, si);
+    __syncthreads();
+    if (w == 0 && j < n) {
+        double2 v = red[0][lane];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) {
+            v.x += red[u][lane].x;
+            v.y += red[u][lane].y;
+        }
+        partial[split * n + j] = v;
+    }
+    if (blockIdx.x != 0) return;
+    double c = 0.0, l = 0.0;
+    for (int64_t s = s_lo + tid; s < s_hi; s += 256) {
+        const double nv = noise_var[s];
+        const double2 ds = d[s];
+        invvar[s] = 1.0 / nv;
+        c += (ds.x * ds.x + ds.y * ds.y) / nv;
+        l += log(nv);
+    }
+    // fixed tree, so that the result does not depend on timing
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        c += __shfl_xor(c, o);
+        l += __shfl_xor(l, o);
+    }
+    __syncthreads();
+    if (lane == 0) red[w][0] = make_double2(c, l);
+    __syncthreads();
+    if (tid == 0) {
+        const double2 a = red[0][0], b = red[1][0], e = red[2][0], f = red[3][0];
+        scal_part[split] = make_double2((a.x + b.x) + (e.x + f.x), (a.y + b.y) + (e.y + f.y));
+    }
 }
 
-// scal[0] = sum_s |d_s|^2 / sigma_s^2, scal[1] = -sum_s ln sigma_s^2 (one
-// workgroup, fixed-order tree so the result does not depend on timing).
-__global__ __launch_bounds__(256) void scalars_kernel(const double2 *__restrict__ d,
-                                                      const double *__restrict__ noise_var, int64_t m,
-                                                      double *__restrict__ scal) {
-    __shared__ double sc[256], sl[256];
-    double c = 0.0, l = 0.0;
-    for (int64_t s = threadIdx.x; s < m; s += 256) {
-        const double2 ds = d[s];
-        c += (ds.x * ds.x + ds.y * ds.y) / noise_var[s];
-        l += log(noise_var[s]);
-    }
-    sc[threadIdx.x] = c;
-    sl[threadIdx.x] = l;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            sc[threadIdx.x] += sc[threadIdx.x + h];
-            sl[threadIdx.x] += sl[threadIdx.x + h];
+// The slices' sums, in order: dbar (zero in the padding), and by one more
+// workgroup scal[0] = sum_s |d_s|^2 / sigma_s^2, scal[1] = -sum_s ln sigma_s^2.
+// A wave per 16 columns, each of its four lane groups a quarter of the slices.
+__global__ __launch_bounds__(64) void vectors_reduce_kernel(const double2 *__restrict__ partial,
+                                                            const double2 *__restrict__ scal_part, int splits,
+                                                            int64_t n, int64_t n_pad, double2 *__restrict__ dbar,
+                                                            double *__restrict__ scal) {
+    const int lane = threadIdx.x, q = lane >> 4;
+    const int64_t j = (int64_t)blockIdx.x * 16 + (lane & 15);
+    const bool last = blockIdx.x == gridDim.x - 1;
+    const int per = (splits + 3) / 4, lo = q * per, hi = min(splits, lo + per);
+    double sr = 0.0, si = 0.0;
+    if (last || j < n) {
+        const double2 *src = last ? scal_part : partial + j;
+        const int64_t step = last ? 1 : n;
+        for (int s = lo; s < hi; ++s) {
+            const double2 v = src[s * step];
+            sr += v.x;
+            si += v.y;
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        scal[0] = sc[0];
-        scal[1] = -sl[0];
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+        sr += __shfl_xor(sr, o);
+        si += __shfl_xor(si, o);
+    }
+    if (last) {
+        if (lane == 0) {
+            scal[0] = sr;
+            scal[1] = -si;
+        }
+    } else if (q == 0 && j < n_pad) {
+        dbar[j] = make_double2(sr, si);
     }
 }
 
@@ -287,6 +326,15 @@ __global__ void export_A_kernel(const double2 *__restrict__ Ap, int64_t n, int64
 void herk_split(int64_t m, int64_t N, int num_cu, int &splits, int64_t &rows_per) {
     const int64_t tiles = n_tiles(N), slots = 2 * (int64_t)(num_cu > 0 ? num_cu : 1);
     splits = 1;
+    if (8 * tiles < slots) {
+        // Eight splits leave workgroups idle: as many as fill them, in slices of
+        // whole tiles of rows. A workgroup takes 0.13 us a row, so at 480 x 200 two
+        // splits took 34 us and eight take 12.
+        rows_per = (m + slots / tiles - 1) / (slots / tiles);
+        rows_per = (rows_per + TS - 1) / TS * TS;
+        splits = (int)((m + rows_per - 1) / rows_per);
+        return;
+    }
     double best = -1.0;
     for (int sp = 1; sp <= 8; ++sp) {
         const int64_t rp = ((m + sp - 1) / sp + TS - 1) / TS * TS;
@@ -329,17 +377,22 @@ hipError_t launch_herk_reduce(const double2 *part, int64_t tiles, int splits, in
     return hipGetLastError();
 }
 
+// Row slices of the vectors: at least 32 rows each, and about eight workgroups
+// per CU over all column blocks.
+int vectors_splits(int64_t m, int64_t n, int num_cu) {
+    const int64_t blocks = (n + 63) / 64, want = (8 * (int64_t)(num_cu > 0 ? num_cu : 1) + blocks - 1) / blocks;
+    return (int)std::max<int64_t>(1, std::min<int64_t>({want, (m + 31) / 32, 512}));
+}
+
 hipError_t launch_precompute_vectors(const Context &c, const double2 *T, int64_t ldT,
                                      const double *noise_var, const double2 *d, double *invvar,
                                      double2 *partial, int splits, hipStream_t s) {
-    hipLaunchKernelGGL(invvar_kernel, dim3((unsigned)((c.m + 255) / 256)), dim3(256), 0, s, noise_var,
-                       c.m, invvar);
     const int64_t rows = (c.m + splits - 1) / splits;
-    hipLaunchKernelGGL(dbar_partial_kernel, dim3((unsigned)((c.n + 255) / 256), (unsigned)splits),
-                       dim3(256), 0, s, T, ldT, c.m, c.n, d, invvar, rows, partial);
-    hipLaunchKernelGGL(dbar_reduce_kernel, dim3((unsigned)((c.n_pad + 255) / 256)), dim3(256), 0, s,
-                       partial, splits, c.n, c.n_pad, c.dbar);
-    hipLaunchKernelGGL(scalars_kernel, dim3(1), dim3(256), 0, s, d, noise_var, c.m, c.scal);
+    double2 *scal_part = partial + (int64_t)splits * c.n;
+    hipLaunchKernelGGL(vectors_kernel, dim3((unsigned)((c.n + 63) / 64), (unsigned)splits), dim3(256), 0, s, T, ldT,
+                       c.m, c.n, noise_var, d, rows, invvar, partial, scal_part);
+    hipLaunchKernelGGL(vectors_reduce_kernel, dim3((unsigned)(c.n_pad / 16 + 1)), dim3(64), 0, s, partial, scal_part,
+                       splits, c.n, c.n_pad, c.dbar, c.scal);
     return hipGetLastError();
 }
 

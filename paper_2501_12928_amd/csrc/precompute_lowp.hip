@@ -15,6 +15,8 @@
 // Both MFMAs return D[4(l/16) + r][l%16] in register r (FP32 16x16x4 and
 // BF16 16x16x32), with the A operand lane l = A[l%16][k-group l/16] and the B
 // operand lane l = B[k-group l/16][l%16].
+#include <algorithm>
+
 #include "common.h"
 
 namespace eor {
@@ -439,7 +441,9 @@ void bf16_split(int64_t m_pad, int64_t N, int num_cu, int &splits, int64_t &rows
     const int64_t tiles = n_tiles(N), slots = num_cu > 0 ? num_cu : 1, chunks = m_pad / CHUNK_ROWS;
     splits = 1;
     double best = 1e300;
-    for (int sp = 1; sp <= 8 && sp <= chunks; ++sp) {
+    // up to eight slices, or as many as give every CU one
+    const int64_t most = std::min(chunks, std::max<int64_t>(8, slots / tiles));
+    for (int sp = 1; sp <= most; ++sp) {
         const int64_t per = (chunks + sp - 1) / sp;
         if ((sp - 1) * per >= chunks) continue;  // no empty slice
         const int64_t rounds = (tiles * sp + slots - 1) / slots;
