@@ -213,16 +213,19 @@ __device__ inline unsigned short bf16_bits(float x) {
 
 __device__ inline float bf16_to_float(unsigned short h) { return __uint_as_float(((unsigned int)h) << 16); }
 
-// Split planes, transposed: plane p (0..5 = re h, m, l, im h, m, l) holds
-// P[p][j][s] for s < m_pad (zero in the padding), so eight consecutive rows
-// s of one column are 16 contiguous bytes. One block transposes a 64 x 64
-// tile of W through LDS.
+// Split planes, transposed and cut into steps of 32 rows: plane p (0..5 = re h,
+// m, l, im h, m, l) of step t holds P[t][p][j][r] for the rows s = 32 t + r <
+// m_pad (zero in the padding), so that a step of 64 columns of one plane, which
+// the product copies to LDS, is 4 KiB in one piece. One block transposes a
+// 64 x 64 tile of W through LDS.
+constexpr int BF_STEP = 32;
+
 template <int NTERM>
 __global__ __launch_bounds__(256) void split_kernel(const double2 *__restrict__ T, int64_t ldT,
                                                     int64_t m, int64_t n,
-                                                    const double *__restrict__ invvar, int64_t m_pad,
-                                                    int64_t n_pad, unsigned short *__restrict__ P) {
-    __shared__ unsigned short sh[2 * NTERM][64][65];
+                                                    const double *__restrict__ invvar, int64_t n_pad,
+                                                    unsigned short *__restrict__ P) {
+    __shared__ __align__(4) unsigned short sh[2 * NTERM][64][66];
     const int64_t s0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int rr = ty; rr < 64; rr += 4) {
@@ -248,18 +251,17 @@ __global__ __launch_bounds__(256) void split_kernel(const double2 *__restrict__ 
         }
     }
     __syncthreads();
-    for (int cc = ty; cc < 64; cc += 4) {
-        const int64_t j = j0 + cc, s = s0 + tx;
-        if (j < n_pad && s < m_pad) {
+    const int col = threadIdx.x >> 2, ch = threadIdx.x & 3;  // 8 rows of a column per thread
 #pragma unroll
-            for (int p = 0; p < 2 * NTERM; ++p) P[((int64_t)p * n_pad + j) * m_pad + s] = sh[p][cc][tx];
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int p = 0; p < 2 * NTERM; ++p) {
+            const unsigned *src = reinterpret_cast<const unsigned *>(&sh[p][col][BF_STEP * t + 8 * ch]);
+            const uint4 v = make_uint4(src[0], src[1], src[2], src[3]);
+            const int64_t step = 2 * (int64_t)blockIdx.y + t;
+            *reinterpret_cast<uint4 *>(P + ((step * 2 * NTERM + p) * n_pad + j0 + col) * BF_STEP + 8 * ch) = v;
         }
     }
-}
-
-__device__ inline bf8 ld_bf8(const unsigned short *p) {
-    const s8v v = *reinterpret_cast<const s8v *>(p);
-    return __builtin_bit_cast(bf8, v);
 }
 
 __device__ inline bf8 neg_bf8(bf8 x) {
@@ -287,141 +289,163 @@ struct Prods<2> {
     static constexpr int Y[3] = {0, 1, 0};
 };
 
-// One workgroup per 64 x 64 tile; per step of 32 rows the workgroup copies
-// both 64-column panels (2 NTERM planes each: 48 KiB for three terms) from
-// HBM into LDS once,
-// and every wave reads its operands there (each wave needs its own 16
-// columns of the row panel and all 64 of the column panel, so reading them
-// straight from memory fetched the column panel four times). Two LDS
-// buffers: the next step's panels are read into registers while this
-// step's are multiplied, and stored after it.
-constexpr int BF_COL = 40;  // LDS stride of a column: 32 rows + 8 pad (bf16)
+// One workgroup of four waves per 128 x 64 block of A: tiles (2 I, j) and
+// (2 I + 1, j). Per step of 32 rows it copies the panels of its 192 columns (2
+// NTERM planes each: 72 KiB for three terms) into one of two LDS buffers; the
+// next step's are read into registers while this step's are multiplied. Wave
+// (wr, wc) owns the 64 rows of tile 2 I + wr and columns 32 wc .. + 31: eight 16
+// x 16 blocks, so that one set of column operands serves four row blocks and
+// one set of row operands two column blocks: 36 KiB of LDS reads per 192 MFMAs
+// of a wave. (With 16 rows and 64 columns per wave, 30 KiB per 96, the LDS time of
+// a step was nearly that of its MFMAs and, with one wave per SIMD, the two added
+// up.) The FP64 sums of eight blocks and the operands in flight take 400
+// registers, which one wave per SIMD has. The 16-byte pieces of a column are
+// stored at piece ^ (column / 2) % 4, which makes the operand reads free of bank
+// conflicts without padding. Each accumulator takes its products in a fixed
+// order. 8000 x 2048, three terms: 953 us against 1042, 900 TFLOP/s where a large
+// library product of the same type reaches 1075 on this card; the whole
+// precompute 1.12 ms against 1.22, 20000 x 4096 8.4 ms against 10.0. Bound by the
+// matrix cores and the clock they leave: reading a row block's operands beside the
+// products of the one before, LDS stores spread likewise, changed nothing (965 us).
+constexpr int BF_COLS = 192;  // columns of a step in LDS: 128 of the rows, 64 of the columns
 
-// Work unit u: tile u % tiles over the 32-row steps of rows [split rows_per,
-// ...), split = u / tiles (rows_per a multiple of CHUNK_ROWS). With one split
-// the tile goes to A; otherwise to its slot of `out` (FP64), and the splits
+// Work unit u: block u % units over the 32-row steps of rows [split rows_per,
+// ...), split = u / units (rows_per a multiple of CHUNK_ROWS). With one split
+// the tiles go to A; otherwise to their slots of `out` (FP64), and the splits
 // are added in a fixed order afterwards.
 template <int NTERM>
-__global__ __launch_bounds__(256) void herk_bf16_kernel(const unsigned short *__restrict__ P,
-                                                        int64_t m_pad, int64_t n_pad, int64_t n, int64_t tiles,
-                                                        int64_t rows_per, int splits,
-                                                        double2 *__restrict__ out) {
-    constexpr int NP = 2 * NTERM;                     // planes: NTERM real, NTERM imaginary
-    constexpr int BF_PANEL = NP * 64 * BF_COL;        // one panel, all planes
-    constexpr int BF_LOADS = 2 * NP * 64 * 4 / 256;   // 16-byte reads per thread per step (12 or 8)
+__global__ __launch_bounds__(256, 1) void herk_bf16_kernel(const unsigned short *__restrict__ P,
+                                                           int64_t m_pad, int64_t n_pad, int64_t n, int64_t units,
+                                                           int64_t rows_per, int splits,
+                                                           double2 *__restrict__ out) {
+    constexpr int NP = 2 * NTERM;   // planes: NTERM real, NTERM imaginary
+    constexpr int NL = 3 * NP;      // 16-byte reads per thread per step: three tiles of columns, NP planes
     using PR = Prods<NTERM>;
-    __shared__ __align__(16) unsigned short lds[2][2 * BF_PANEL];
-    const int64_t tile = blockIdx.x % tiles, split = blockIdx.x / tiles;
+    __shared__ __align__(16) unsigned short lds[2][NP * BF_COLS * BF_STEP];
+    const int64_t unit = blockIdx.x % units, split = blockIdx.x / units;
     const int64_t r0 = split * rows_per;
     const int64_t r1 = r0 + rows_per < m_pad ? r0 + rows_per : m_pad;
-    int64_t ti, tj;
-    tile_of(tile, ti, tj);
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q = lane >> 4;
-    const int64_t plane = n_pad * m_pad;
-    // the thread's share of a step: 16 bytes (8 rows) of one column of one
-    // plane of one panel; e = ((panel * NP + p) * 64 + col) * 4 + 8-row group
-    // = tid + 256 u, so read u is plane u % NP of panel u / NP, at the
-    // thread's own column and row group. Two column bases per thread and
-    // offsets that are uniform per read (the plane), rather than a pointer
-    // and an LDS offset per read: fewer registers live through the loop.
-    const int g8 = tid & 3, col = (tid >> 2) & 63;
-    const unsigned short *base[2] = {P + (TS * ti + col) * m_pad + 8 * g8, P + (TS * tj + col) * m_pad + 8 * g8};
-    const int dthr = col * BF_COL + 8 * g8;
-    s8v pre[BF_LOADS];
-    auto fetch = [&](int64_t s0) {
+    // unit = I (I + 1) + j, j <= 2 I + 1
+    int64_t I = (int64_t)((sqrt(4.0 * (double)unit + 1.0) - 1.0) * 0.5);
+    while (I * (I + 1) > unit) --I;
+    while ((I + 1) * (I + 2) <= unit) ++I;
+    const int64_t tj = unit - I * (I + 1), N = n_pad / TS;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w & 1, wc = w >> 1;
+    // the thread's piece of a 64-column group: column tid / 4, rows 8 (tid % 4) ..
+    const int col = tid >> 2, ch = tid & 3;
+    const int64_t tiles[3] = {2 * I, 2 * I + 1 < N ? 2 * I + 1 : 2 * I, tj};  // a missing tile reads another and is not stored
+    int voff[3];
 #pragma unroll
-        for (int u = 0; u < BF_LOADS; ++u)
-            pre[u] = *reinterpret_cast<const s8v *>(base[u / NP] + (int64_t)(u % NP) * plane + s0);
+    for (int g = 0; g < 3; ++g) voff[g] = (int)((TS * tiles[g] + col) * (BF_STEP * 2)) + 16 * ch;
+    const int dst = col * BF_STEP + 8 * (ch ^ ((col >> 1) & 3));
+    s8v pre[NL];
+    auto fetch = [&](int64_t s0) {
+        const rsrc_t R = make_rsrc(P + (s0 / BF_STEP) * NP * n_pad * BF_STEP, NP * n_pad * BF_STEP * 2);
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+            pre[u] = __builtin_bit_cast(s8v, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 R, voff[u % 3], (int)((u / 3) * n_pad * (BF_STEP * 2)), 0));
     };
     auto stash = [&](int b) {
 #pragma unroll
-        for (int u = 0; u < BF_LOADS; ++u)
-            *reinterpret_cast<s8v *>(&lds[b][(u / NP) * BF_PANEL + (u % NP) * 64 * BF_COL + dthr]) = pre[u];
+        for (int u = 0; u < NL; ++u)
+            *reinterpret_cast<s8v *>(&lds[b][((u / 3) * BF_COLS + TS * (u % 3)) * BF_STEP + dst]) = pre[u];
     };
-    // B operand a = W[s][64 ti + 16 w + l16] (panel 0), A operands b = W[s][64 tj + 16 cb + l16] (panel 1)
-    auto opnd = [&](int b, int panel, int p, int col) {
-        return __builtin_bit_cast(bf8, *reinterpret_cast<const s8v *>(
-                                           &lds[b][panel * BF_PANEL + (p * 64 + col) * BF_COL + 8 * q]));
+    // operand of plane p: column c0 + l16 of the step (c0 a multiple of 16), rows 8 q ..
+    const int opn = l16 * BF_STEP + 8 * (q ^ ((l16 >> 1) & 3));
+    auto opnd = [&](int b, int p, int c0) {
+        return __builtin_bit_cast(bf8, *reinterpret_cast<const s8v *>(&lds[b][(p * BF_COLS + c0) * BF_STEP + opn]));
     };
-    double sR[4][4], sI[4][4];
+    double sR[4][2][4], sI[4][2][4];
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
+    for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sR[cb][r] = sI[cb][r] = 0.0;
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sR[rb][cb][r] = sI[rb][cb][r] = 0.0;
 
     fetch(r0);
     stash(0);
     __syncthreads();
-    int buf = 0;
     for (int64_t c0 = r0; c0 < r1; c0 += CHUNK_ROWS) {
-        f4 aR[4], aI[4];
+        f4 aR[4][2], aI[4][2];
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            aR[cb] = f4{0, 0, 0, 0};
-            aI[cb] = f4{0, 0, 0, 0};
-        }
-        for (int64_t s0 = c0; s0 < c0 + CHUNK_ROWS; s0 += 32) {
-            const bool more = s0 + 32 < r1;
-            if (more) fetch(s0 + 32);
-            bf8 ar[NTERM], ai[NTERM], nai[NTERM];
+        for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-            for (int t = 0; t < NTERM; ++t) {
-                ar[t] = opnd(buf, 0, t, 16 * w + l16);
-                ai[t] = opnd(buf, 0, NTERM + t, 16 * w + l16);
-                nai[t] = neg_bf8(ai[t]);
+            for (int cb = 0; cb < 2; ++cb) {
+                aR[rb][cb] = f4{0, 0, 0, 0};
+                aI[rb][cb] = f4{0, 0, 0, 0};
             }
-            // re: br ar + bi ai;  im: bi ar - br ai. Two 16-column blocks at a
-            // time, the products of their four accumulators issued in turn so
-            // that no product waits on the one before it; each accumulator
-            // still takes its twelve products in the same order
 #pragma unroll
-            for (int cp = 0; cp < 4; cp += 2) {
-                bf8 br[2][NTERM], bi[2][NTERM];
+        for (int b = 0; b < CHUNK_ROWS / BF_STEP; ++b) {  // two steps: LDS buffers 0 and 1
+            const int64_t next = c0 + BF_STEP * (b + 1);
+            if (next < r1) fetch(next);
+            bf8 br[2][NTERM], bi[2][NTERM];
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+            for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                    for (int t = 0; t < NTERM; ++t) {
-                        br[h][t] = opnd(buf, 1, t, 16 * (cp + h) + l16);
-                        bi[h][t] = opnd(buf, 1, NTERM + t, 16 * (cp + h) + l16);
+                for (int t = 0; t < NTERM; ++t) {
+                    br[cb][t] = opnd(b, t, 2 * TS + 32 * wc + 16 * cb);
+                    bi[cb][t] = opnd(b, NTERM + t, 2 * TS + 32 * wc + 16 * cb);
+                }
+            // re: br ar + bi ai;  im: bi ar - br ai
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb) {
+                bf8 ar[NTERM], ai[NTERM], nai[NTERM];
+#pragma unroll
+                for (int t = 0; t < NTERM; ++t) {
+                    ar[t] = opnd(b, t, TS * wr + 16 * rb);
+                    ai[t] = opnd(b, NTERM + t, TS * wr + 16 * rb);
+                    nai[t] = neg_bf8(ai[t]);
+                }
+#pragma unroll
+                for (int e = 0; e < PR::N; ++e)
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        aR[rb][cb] = mfma_bf16(br[cb][PR::X[e]], ar[PR::Y[e]], aR[rb][cb]);
+                        aI[rb][cb] = mfma_bf16(bi[cb][PR::X[e]], ar[PR::Y[e]], aI[rb][cb]);
                     }
 #pragma unroll
                 for (int e = 0; e < PR::N; ++e)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        aR[cp + h] = mfma_bf16(br[h][PR::X[e]], ar[PR::Y[e]], aR[cp + h]);
-                        aI[cp + h] = mfma_bf16(bi[h][PR::X[e]], ar[PR::Y[e]], aI[cp + h]);
-                    }
-#pragma unroll
-                for (int e = 0; e < PR::N; ++e)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        aR[cp + h] = mfma_bf16(bi[h][PR::X[e]], ai[PR::Y[e]], aR[cp + h]);
-                        aI[cp + h] = mfma_bf16(br[h][PR::X[e]], nai[PR::Y[e]], aI[cp + h]);
+                    for (int cb = 0; cb < 2; ++cb) {
+                        aR[rb][cb] = mfma_bf16(bi[cb][PR::X[e]], ai[PR::Y[e]], aR[rb][cb]);
+                        aI[rb][cb] = mfma_bf16(br[cb][PR::X[e]], nai[PR::Y[e]], aI[rb][cb]);
                     }
             }
-            if (more) stash(buf ^ 1);
+            if (next < r1) stash(b ^ 1);
             __syncthreads();
-            buf ^= 1;
         }
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sR[rb][cb][r] += (double)aR[rb][cb][r];
+                    sI[rb][cb][r] += (double)aI[rb][cb][r];
+                }
+    }
+    // lane holds [16 rb + l16][32 wc + 16 cb + 4 q + r] of tile (2 I + wr, j)
+    const int64_t ti = 2 * I + wr;
+    if (ti >= N || tj > ti) return;
+    double2 *pt = splits == 1 ? out + tile_index(ti, tj) * TS2 : out + (split * n_tiles(N) + tile_index(ti, tj)) * TS2;
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sR[cb][r] += (double)aR[cb][r];
-                sI[cb][r] += (double)aI[cb][r];
+                const int row = 16 * rb + l16, c = 32 * wc + 16 * cb + 4 * q + r;
+                const int64_t grow = TS * ti + row, gcol = TS * tj + c;
+                double2 v = make_double2(sR[rb][cb][r], sI[rb][cb][r]);
+                if (splits == 1) {
+                    if (grow == gcol) v.y = 0.0;
+                    if (grow >= n || gcol >= n) v = make_double2(grow == gcol ? 1.0 : 0.0, 0.0);
+                }
+                pt[c * TS + row] = v;
             }
-    }
-    if (splits == 1) {
-        store_tile(out, ti, tj, n, sR, sI, w, l16, q);
-        return;
-    }
-    // partial tile, column-major: lane holds [16 w + l16][16 cb + 4 q + r]
-    double2 *pt = out + (split * tiles + tile) * TS2;
-    const int row = 16 * w + l16;
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pt[(16 * cb + 4 * q + r) * TS + row] = make_double2(sR[cb][r], sI[cb][r]);
 }
 
 }  // namespace
@@ -432,22 +456,30 @@ void fp32_split(int64_t m_pad, int64_t N, int num_cu, int &splits, int64_t &rows
     rows_per = (rows_per + CHUNK_ROWS - 1) / CHUNK_ROWS * CHUNK_ROWS;
 }
 
-// Row slices of the split-BF16 product. Its workgroups hold 120 KiB of LDS,
-// one per CU, so a round is num_cu units; the slices (whole chunks) are
-// chosen to minimise the chunk steps of the busiest CU, rounds x chunks per
-// slice, each extra slice counted as half a chunk step per unit for its
-// partial tile and its share of the reduction.
+// Blocks of 128 x 64 of the lower triangle: pairs of tile rows 2 I, 2 I + 1
+// against tile columns j <= 2 I + 1 (a missing last tile row drops its own column).
+int64_t bf16_units(int64_t N) { return (N / 2) * (N / 2 + 1) + (N % 2 ? N : 0); }
+
+// Row slices of the split-BF16 product. Its workgroups fill a CU each, so a
+// round is num_cu units; the slices (whole chunks) are chosen to minimise the
+// chunks of the busiest CU, rounds x chunks per slice, at BF_CHUNK_US each, and
+// 0.03 us per tile and slice for writing and adding its partial tiles. Measured:
+// a chunk is 192 x 2 MFMAs of a wave, 2.6 us, plus its copies and FP64 sums; at
+// 8000 x 2048 (272 blocks on 256 CUs) one slice would leave the second round
+// nearly empty and cost 2 x 125 chunks, eight cost 9 x 16.
+constexpr double BF_CHUNK_US = 3.3;
+
 void bf16_split(int64_t m_pad, int64_t N, int num_cu, int &splits, int64_t &rows_per) {
-    const int64_t tiles = n_tiles(N), slots = num_cu > 0 ? num_cu : 1, chunks = m_pad / CHUNK_ROWS;
+    const int64_t units = bf16_units(N), slots = num_cu > 0 ? num_cu : 1, chunks = m_pad / CHUNK_ROWS;
     splits = 1;
     double best = 1e300;
     // up to eight slices, or as many as give every CU one
-    const int64_t most = std::min(chunks, std::max<int64_t>(8, slots / tiles));
+    const int64_t most = std::min(chunks, std::max<int64_t>(8, slots / units));
     for (int sp = 1; sp <= most; ++sp) {
         const int64_t per = (chunks + sp - 1) / sp;
         if ((sp - 1) * per >= chunks) continue;  // no empty slice
-        const int64_t rounds = (tiles * sp + slots - 1) / slots;
-        const double cost = (double)rounds * (double)per + (sp > 1 ? 0.5 * (double)rounds : 0.0);
+        const int64_t rounds = (units * sp + slots - 1) / slots;
+        const double cost = (double)rounds * (double)per * BF_CHUNK_US + (sp > 1 ? 4.0 + 0.03 * (double)(sp * n_tiles(N)) : 0.0);
         if (cost < best - 1e-9) {
             best = cost;
             splits = sp;
@@ -505,14 +537,15 @@ hipError_t launch_precompute_bf16(const Context &c, const double2 *T, int64_t ld
     double2 *part = splits > 1 ? (double2 *)((char *)scratch + (size_t)(2 * nterm) * m_pad * c.n_pad *
                                                                  sizeof(unsigned short))
                                : c.A;
-    const dim3 hgrid((unsigned)(tiles * splits));
+    const int64_t units = bf16_units(c.N);
+    const dim3 hgrid((unsigned)(units * splits));
     if (nterm == 3) {
-        hipLaunchKernelGGL(split_kernel<3>, sgrid, dim3(256), 0, s, T, ldT, c.m, c.n, invvar, m_pad, c.n_pad, P);
-        hipLaunchKernelGGL(herk_bf16_kernel<3>, hgrid, dim3(256), 0, s, P, m_pad, c.n_pad, c.n, tiles, rows_per,
+        hipLaunchKernelGGL(split_kernel<3>, sgrid, dim3(256), 0, s, T, ldT, c.m, c.n, invvar, c.n_pad, P);
+        hipLaunchKernelGGL(herk_bf16_kernel<3>, hgrid, dim3(256), 0, s, P, m_pad, c.n_pad, c.n, units, rows_per,
                            splits, part);
     } else {
-        hipLaunchKernelGGL(split_kernel<2>, sgrid, dim3(256), 0, s, T, ldT, c.m, c.n, invvar, m_pad, c.n_pad, P);
-        hipLaunchKernelGGL(herk_bf16_kernel<2>, hgrid, dim3(256), 0, s, P, m_pad, c.n_pad, c.n, tiles, rows_per,
+        hipLaunchKernelGGL(split_kernel<2>, sgrid, dim3(256), 0, s, T, ldT, c.m, c.n, invvar, c.n_pad, P);
+        hipLaunchKernelGGL(herk_bf16_kernel<2>, hgrid, dim3(256), 0, s, P, m_pad, c.n_pad, c.n, units, rows_per,
                            splits, part);
     }
     if (splits > 1) return launch_herk_reduce(part, tiles, splits, c.n, c.A, s);
