@@ -70,6 +70,28 @@ __device__ inline void store_word(int32_t *p, int v) {
     __hip_atomic_store((gword *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ inline void wait_vmem() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+}
+
+// Everything the workgroup's waves have stored and waited for becomes visible
+// to the other XCDs. The fence starts a write-back of the XCD's L2
+// (buffer_wbl2), which the compiler does not count among the operations that a
+// following store waits for once no store of the wave itself is pending: left
+// to it, the word that announces a tile could be seen before the tile (1 theta
+// in 4000 at n = 1030 came out with a stale line). Waited for explicitly.
+__device__ inline void release() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    wait_vmem();
+}
+
+// The same for the invalidation that an acquire starts (buffer_inv): complete
+// before the barrier that lets the workgroup's other waves load.
+__device__ inline void acquire() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    wait_vmem();
+}
+
 // Until rows i and j both have more than k finished tiles: the smaller of the
 // two counts, or -1 if the theta has failed. Called by the whole workgroup;
 // what the finished tiles' units wrote is visible afterwards.
@@ -87,7 +109,7 @@ __device__ inline int wait_tiles(const int32_t *prog, int stop, int i, int j, in
             else
                 __builtin_amdgcn_s_sleep(127);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        acquire();
         *seen = v;
     }
     __syncthreads();
@@ -98,10 +120,10 @@ __device__ inline int wait_tiles(const int32_t *prog, int stop, int i, int j, in
 
 // Every wave's stores so far become visible, then word = v.
 __device__ inline void publish(int32_t *word, int v) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    wait_vmem();
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        release();
         store_word(word, v);
     }
 }
@@ -319,10 +341,10 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     publish(prog + j, j + 1);
                     // beside the chain of diagonal tiles: the column's ln d
                     if (q == 1) *lnd_of(L, j, row) = log(sh.dg[row]);
-                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    wait_vmem();
                     __syncthreads();
                     if (tid == 0) {
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                        release();
                         atomicAdd(prog + a.n_max + 1, 1);
                     }
                 } else {
@@ -350,6 +372,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         if (threadIdx.x == 0) {
             // released, so that no store of this unit to the words can land after they are cleared
             int32_t *done = prog + a.n_max + 2;
+            wait_vmem();
             const int before = __hip_atomic_fetch_add((gword *)done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
             if (before == N * (N + 1) / 2 - 1) {
                 for (int e = 0; e < a.n_max + SPREAD_EXTRA; ++e) store_word(prog + e, 0);

@@ -49,6 +49,27 @@ def test_same_bits_in_any_batch(orc, m, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("m,n,calls", [(500, 300, 400), (1300, 1030, 800)])
+def test_same_bits_in_every_call(m, n, calls):
+    """Tiles pass between workgroups on different XCDs: no call may see one
+    before it is complete. (Where the write-back of a workgroup's L2 was not
+    waited for, one theta in 4000 at n = 1030 differed.)"""
+    import torch
+    inst = synth.small(seed=n, m=m, n=n, n_k=4, n_theta=256)
+    ctx = _ctx(inst)
+    t = torch.from_numpy(inst.theta).cuda()
+    print(f"gpu: n={n}, {calls} calls", flush=True)
+    whole, _, terms = ctx.loglike_terms(t)
+    rng = np.random.default_rng(n)
+    for _ in range(calls):
+        B = int(rng.integers(1, 24))
+        at = int(rng.integers(0, 256 - B))
+        part, info, pterms = ctx.loglike_terms(t[at:at + B])
+        assert torch.equal(part, whole[at:at + B]) and torch.equal(pterms, terms[at:at + B])
+        assert not info.any()
+    ctx.close()
+
+
 @pytest.mark.parametrize("col", [0, 63, 64, 130, 191, 192, 299])
 def test_failed_pivot_then_good_call(col):
     """A pivot that fails in any tile column is reported for every theta, and
