@@ -38,6 +38,7 @@ struct eor_group {
     int32_t *prog = nullptr;             // progress words, zero between launches
     int64_t spread_rows = 0, spread_elems = 0, spread_units = 0;
     double est_spread = 0.0, est_lone = 0.0;
+    int spread_per_cu = 2;
     std::vector<int64_t> task_B, task_N; // B and tile rows per instance the task list was built for
     unsigned int *counter = nullptr;
     double2 *Lw = nullptr;
@@ -158,6 +159,7 @@ hipError_t build_spread(eor_group &g, const std::vector<int2> &tasks) {
     }
     for (int64_t r = N_max; r > 0; --r) count[r - 1] += count[r];
     g.est_spread = eor::spread_us(chain, work);
+    g.spread_per_cu = eor::spread_per_cu(chain, work);
     g.spread_rows = N_max;
     g.spread_elems = elems;
     g.spread_units = units;
@@ -310,6 +312,7 @@ eor::SpreadParams make_spread(const eor_group &g, const double *const *theta, do
     p.ntask = (int32_t)g.ntask;
     p.n_max = (int32_t)g.spread_rows;
     p.units = g.spread_units;
+    p.per_cu = g.spread_per_cu;
     p.counter = g.counter;
     p.prog = g.prog;
     p.Lw = g.Lw;

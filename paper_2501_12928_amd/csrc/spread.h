@@ -8,8 +8,9 @@ namespace eor {
 
 // Words of one theta's progress row beside the N counts of finished tiles:
 // stop (the theta has failed), tails (diagonal tiles whose ln d is stored),
-// done (finished units).
-constexpr int SPREAD_EXTRA = 3;
+// done (finished units), handed (the last row whose X is in its diagonal
+// tile's slot).
+constexpr int SPREAD_EXTRA = 4;
 
 struct SpreadParams {
     const InstDesc *inst;    // device [n_inst]
@@ -25,6 +26,7 @@ struct SpreadParams {
     int64_t slot_elems;
     double2 *yw;             // per-slot w, then y
     int64_t slot_y;
+    int32_t per_cu;          // workgroups per CU, 1 or 2 (spread_per_cu)
     CallDesc call[MAX_INST];
 };
 
@@ -36,14 +38,23 @@ hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s);
 //  - one workgroup takes a theta of N tile rows in 30 N + 1.5 N^2 + 0.93 N^3
 //    (200 us at n = 200, 4.7 ms at 1003, 253 ms at 4096), up to 15% more when
 //    all workgroups run;
-inline double lone_us(int64_t N) { return 30.0 * N + 1.5 * N * N + 0.93 * N * N * N; }
-//  - spread, a theta's diagonal tiles follow one another every 34 us, and its
+//  - spread, a theta's diagonal tiles follow one another every 30 us, and its
 //    N (N + 1) / 2 tiles take the whole GPU 0.08 us each plus their products at
-//    78 TFLOP/s. The chain and the work of all theta overlap in part.
-inline double spread_chain_us(int64_t N) { return 34.0 * N; }
+//    78 TFLOP/s. The chain and the work of all theta overlap almost wholly where
+//    the chain is the longer, in part otherwise.
+inline double lone_us(int64_t N) { return 30.0 * N + 1.5 * N * N + 0.93 * N * N * N; }
+inline double spread_chain_us(int64_t N) { return 30.0 * N; }
 inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 * 262144.0 * N * N * N / 78e6; }
 inline double spread_us(double chain, double work) {
-    return chain > work ? chain + 0.3 * work : work + 0.3 * chain;
+    return chain > work ? chain + 0.1 * work : work + 0.3 * chain;
 }
+
+// Where the chain bounds, one workgroup per CU: a second one's matrix
+// instructions hold up the single wave that factors a diagonal tile (19 us
+// beside them, 14 alone). One against two per CU: n = 4096, one theta 1.93
+// against 2.30 ms, two 2.83 / 2.98, four 5.06 / 4.99; n = 2048, four 1.04 / 1.19,
+// 16 3.04 / 2.82; n = 1003, eight 498 / 570 us, 16 633 / 684, 24 881 / 793; n =
+// 200, 128 theta (the work 1.17 times the chain) 241 / 226.
+inline int spread_per_cu(double chain, double work) { return work < 1.1 * chain ? 1 : 2; }
 
 }  // namespace eor

@@ -30,14 +30,20 @@
 // stop word, its other units return at their next wait, and the last unit
 // of a theta clears its progress words for the next launch.
 //
-// What bounds it: with one theta the chain from one diagonal tile to the next,
-// 34 us (factor 13.7, its stores 1.5, seen and loaded 2, tile below 5.1, last
-// update and move to LDS 11.4): one theta at n = 4096 253 -> 2.4 ms, at n =
-// 2048 33.5 -> 1.1 ms, at n = 200 190 -> 130 us. With many theta the FP64
-// matrix cores and the panels' traffic (each unit streams both of its panels
-// alone): 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79 with 256
-// theta of one workgroup each, where two tiles share a panel; so full rounds
-// stay there (spread_count in abi.hip, build_spread in runtime.hip).
+// What bounds it: with few theta the chain from one diagonal tile to the next.
+// Tile (j+1, j) would be formed, announced and read back between the two;
+// instead its unit hands over X (what Linv_jj is still to be applied to) while
+// tile (j, j) is being factored, and the unit of tile (j+1, j+1) forms L_(j+1)j
+// itself and updates from LDS (last_update): 37 -> 31 us per column (factor 14.4,
+// y and stores 2, announced, seen and loaded 3, tile below 4.4, update and move
+// to LDS 7). With one workgroup per CU (spread_per_cu) one theta at n = 4096 takes
+// 1.93 ms (253 by one workgroup, 2.46 with tile (j+1, j) read back and two per CU),
+// at n = 2048 0.95 (33.5, 1.12), at n = 200 130 us (190, 134). With many theta
+// the FP64 matrix cores and the panels' traffic (each unit streams both of its
+// panels alone) bound: 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79
+// with 256 theta of one workgroup each, where two tiles share a panel; so full
+// rounds stay there (spread_count in abi.hip, build_spread in runtime.hip). There
+// nothing is handed over: with it 24 theta at n = 1003 took 800 us, 784 without.
 #include <algorithm>
 
 #include "like_device.h"
@@ -157,14 +163,15 @@ __device__ __forceinline__ void accumulate(rsrc_t P, rsrc_t Q, int k0, int k1, i
     } while (c < end);
 }
 
-// X of tile (i, j) in the accumulator layout; false if the theta has failed.
-__device__ __forceinline__ bool spread_update(SpreadShared &sh, const double2 *A, const double2 *L, const int32_t *prog,
-                                              int stop, int i, int j, int w, d4 xr[4], d4 xi[4]) {
+// Accumulators of X = A_ij - sum_{k < kend} L_ik L_jk^H as the tiles finish
+// (kend <= j), in tile_update's form: t1, xr = T2, t3; false if the theta has
+// failed.
+__device__ __forceinline__ bool spread_sum(SpreadShared &sh, const double2 *A, const double2 *L, const int32_t *prog,
+                                           int stop, int i, int j, int kend, int w, d4 t1[4], d4 xr[4], d4 t3[4]) {
     const int lane = opaque(threadIdx.x & 63), l16 = lane & 15, q = lane >> 4;
     const int64_t aoff = tile_index(i, j) * TS2 + 16 * w;
     const rsrc_t Ar = make_rsrc(A + aoff, (int64_t)(TS2 - 16 * w) * 16);
     const int voff = (q * TS + l16) * 16;
-    d4 t1[4], t3[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
 #pragma unroll
@@ -178,30 +185,34 @@ __device__ __forceinline__ bool spread_update(SpreadShared &sh, const double2 *A
     for (int cb = 0; cb < 4; ++cb) {
         t1[cb] = d4{0, 0, 0, 0};
         t3[cb] = xr[cb] - t3[cb];
-        xr[cb] = -xr[cb];  // T2
+        xr[cb] = -xr[cb];
     }
-    const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * TS2 + 16 * w, (int64_t)j * TS * COLB);
-    const rsrc_t Qr = make_rsrc(L + tile_index(j, 0) * TS2, (int64_t)j * TS * COLB);
+    const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * TS2 + 16 * w, (int64_t)kend * TS * COLB);
+    const rsrc_t Qr = make_rsrc(L + tile_index(j, 0) * TS2, (int64_t)kend * TS * COLB);
     bool ok = true;
-    if (j > 0) {
+    if (kend > 0) {
         int k = 0;
 #pragma unroll 1
         do {
             const int v = wait_tiles(prog, stop, i, j, k, i <= j + 1 ? j - k - 1 : j - k, &sh.seen);
             ok = v >= 0;
             if (!ok) break;
-            const int e = min(v, j);
+            const int e = min(v, kend);
             accumulate(Pr, Qr, k, e, voff, t1, xr, t3);
             k = e;
-        } while (k < j);
+        } while (k < kend);
     }
+    return ok;
+}
+
+// X from its accumulators: real part into xr = T2, imaginary part into t3.
+__device__ __forceinline__ void spread_x(const d4 t1[4], d4 xr[4], d4 t3[4]) {
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
         const d4 a = t1[cb], b = xr[cb];
         xr[cb] = -(a + b);
-        xi[cb] = a - b - t3[cb];
+        t3[cb] = a - b - t3[cb];
     }
-    return ok;
 }
 
 // Where the unit of diagonal tile j leaves ln d of a row: in the tile's slot of
@@ -216,6 +227,89 @@ __device__ inline void lower_block(int b, int tid, int &row, int &col) {
     const int bi = b < 1 ? 0 : b < 3 ? 1 : b < 6 ? 2 : 3, bj = b - bi * (bi + 1) / 2;
     row = 16 * bi + (tid & 15);
     col = 16 * bj + (tid >> 4);
+}
+
+// Linv_jj, once published, into Dt.
+__device__ __forceinline__ void load_linv(SpreadShared &sh, const double2 *L, int j, int tid) {
+    const double2 *V = L + tile_index(j, j) * TS2;
+    double2 v[10];
+#pragma unroll
+    for (int b = 0; b < 10; ++b) {
+        int row, col;
+        lower_block(b, tid, row, col);
+        v[b] = ldd2(V + col * TS + row);
+    }
+#pragma unroll
+    for (int b = 0; b < 10; ++b) {
+        int row, col;
+        lower_block(b, tid, row, col);
+        sh.Dt[col * (TS + 1) + row] = v[b];
+    }
+}
+
+// The last update of diagonal tile j, k = j - 1, with the tile L_jk formed
+// here as well: its unit hands over X = L_jk Linv_kk^-H in tile (j, j)'s slot of
+// L while Linv_kk is still being computed, so that from Linv_kk to this
+// update nothing passes between workgroups. t1, t2, t3 += L_jk L_jk^H. False if
+// the theta has failed.
+__device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, const int32_t *prog, int stop, int j,
+                                            int w, d4 t1[4], d4 t2[4], d4 t3[4]) {
+    constexpr int LD = TS + 1;
+    if (wait_tiles(prog, stop, stop + 3, stop + 3, j - 1, 1, &sh.seen) < 0) return false;
+    const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+    d4 xr[4], xi[4];
+    const double2 *X = L + tile_index(j, j) * TS2 + tid;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double2 v = ldd2(X + (4 * cb + r) * 256);
+            xr[cb][r] = v.x;
+            xi[cb][r] = v.y;
+        }
+    if (wait_tiles(prog, stop, j - 1, j - 1, j - 1, 0, &sh.seen) < 0) return false;
+    load_linv(sh, L, j - 1, tid);
+    __syncthreads();
+    // Y = X Linv^H as in tile_below, last column block first: it alone needs all of X
+    d4 yr[4], yi[4];
+    const int lt = q * LD + l16;
+#pragma unroll
+    for (int cb2 = 3; cb2 >= 0; --cb2) {
+        d4 s1 = d4{0, 0, 0, 0}, s2 = d4{0, 0, 0, 0}, s3 = d4{0, 0, 0, 0};
+#pragma unroll
+        for (int cb = 0; cb <= cb2; ++cb) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double2 lv = sh.Dt[lt + (16 * cb + 4 * r) * LD + 16 * cb2];
+                const double ar = xr[cb][r], ai = xi[cb][r];
+                s1 = mfma64(ar, lv.x, s1);
+                s2 = mfma64(ai, lv.y, s2);
+                s3 = mfma64(ar + ai, lv.x - lv.y, s3);
+            }
+        }
+        yr[cb2] = s1 + s2;
+        yi[cb2] = s3 - s1 + s2;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    // lane holds Y[16w + q + 4r][16 cb + l16]
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            sh.Dt[(16 * cb + l16) * LD + 16 * w + q + 4 * r] = make_double2(yr[cb][r], yi[cb][r]);
+    __syncthreads();
+#pragma unroll 2
+    for (int c = 0; c < TS; c += 4) {
+        Step<4> s;
+        const double2 *col = sh.Dt + (c + q) * LD + l16;
+        s.p = col[16 * w];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) s.qv[cb] = col[16 * cb];
+        mma_step(s, t1, t2, t3);
+    }
+    __syncthreads();
+    return true;
 }
 
 // Two workgroups per CU: four waves of 256 registers each, and while one waits
@@ -257,28 +351,30 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         const double2 *A = uniform_ptr(I.A);
         double2 *L = uniform_ptr(a.Lw + (a.off ? a.off[slot] : slot * a.slot_elems)), *yv = uniform_ptr(a.yw + slot * a.slot_y);
         int32_t *prog = uniform_ptr(a.prog + (int64_t)slot * (a.n_max + SPREAD_EXTRA));
+        const bool hand = a.per_cu == 1;
         d4 xr[4], xi[4];
         if (u <= 1) __builtin_amdgcn_s_setprio(2);
         if (u > 0) {
-            bool ok = spread_update(sh, A, L, prog, stop, i, j, w, xr, xi);
+            bool ok;
+            {
+                d4 t1[4];
+                ok = spread_sum(sh, A, L, prog, stop, i, j, j, w, t1, xr, xi);
+                spread_x(t1, xr, xi);
+            }
+            if (ok && u == 1 && hand) {  // to the unit of diagonal tile i (last_update)
+                const int tid = opaque(threadIdx.x);
+                double2 *X = L + tile_index(i, i) * TS2 + tid;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) std2(X + (4 * cb + r) * 256, xr[cb][r], xi[cb][r]);
+                publish(prog + stop + 3, i);
+            }
             if (ok) ok = wait_tiles(prog, stop, j, j, j, 0, &sh.seen) >= 0;  // Linv_jj and y_j
             if (ok) {
                 const int tid = opaque(threadIdx.x);
-                const double2 *V = L + tile_index(j, j) * TS2;
-                double2 v[10];
-#pragma unroll
-                for (int b = 0; b < 10; ++b) {
-                    int row, col;
-                    lower_block(b, tid, row, col);
-                    v[b] = ldd2(V + col * TS + row);
-                }
                 if (tid < TS) sh.ys[tid] = ldd2(yv + j * TS + tid);
-#pragma unroll
-                for (int b = 0; b < 10; ++b) {
-                    int row, col;
-                    lower_block(b, tid, row, col);
-                    sh.Dt[col * (TS + 1) + row] = v[b];
-                }
+                load_linv(sh, L, j, tid);
                 __syncthreads();
                 double2 *wi = yv + i * TS;
                 tile_below<TS>(sh.Dt, sh.ys, xr, xi, L + tile_index(i, j) * TS2, j == 0 ? I.dbar + i * TS : wi, wi, w);
@@ -300,10 +396,14 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     store_word(prog + stop, 1);
                 }
             }
-            if (ok) ok = spread_update(sh, A, L, prog, stop, j, j, w, xr, xi);
+            if (ok) {
+                d4 t1[4];
+                ok = spread_sum(sh, A, L, prog, stop, j, j, hand && j > 0 ? j - 1 : j, w, t1, xr, xi);
+                if (ok && hand && j > 0) ok = last_update(sh, L, prog, stop, j, w, t1, xr, xi);
+                spread_x(t1, xr, xi);
+            }
             if (ok) {
                 const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
-                if (tid < TS) sh.wv[tid] = ldd2(j == 0 ? I.dbar + tid : yv + j * TS + tid);
                 const int lo = q * (TS + 1) + 16 * w + l16;  // [16w + l16][q]
 #pragma unroll
                 for (int cb = 0; cb < 4; ++cb) {
@@ -324,9 +424,13 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     }
                 }
             }
+            // w_j, which tile (j, j - 1) completes beside the factorisation
+            if (ok && j > 0) ok = wait_tiles(prog, stop, j, j, j - 1, 0, &sh.seen) >= 0;
             if (ok) {
                 const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
                 const int row = 16 * w + l16;
+                if (tid < TS) sh.wv[tid] = ldd2(j == 0 ? I.dbar + tid : yv + j * TS + tid);
+                __syncthreads();
                 const double2 y = tile_solve<TS>(sh.Dt, sh.wv, w, l16, q);
                 if (q == 0) std2(yv + j * TS + row, y.x, y.y);
                 if (j < N - 1) {
@@ -384,7 +488,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
 }  // namespace
 
 hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s) {
-    const int64_t grid = std::min<int64_t>(p.units, 2 * (int64_t)num_cu);
+    const int64_t grid = std::min<int64_t>(p.units, (int64_t)p.per_cu * num_cu);
     if (grid < 1) return hipSuccess;
     hipLaunchKernelGGL(spread_kernel, dim3((unsigned)grid), dim3(256), 0, s, p);
     return hipGetLastError();
