@@ -43,6 +43,7 @@ InstDesc inst_desc(const Context &c) {
     d.fixed_logv = c.fixed_logv;
     d.n_k = c.n_k;
     d.N = (int32_t)c.N;
+    d.n = (int32_t)c.n;
     d.ts = c.tune.ts;
     return d;
 }

@@ -42,6 +42,7 @@ struct InstDesc {
     int32_t n_k;
     int32_t N;                 // 64-wide storage tiles per side
     int32_t ts;                // side of the factorisation tiles of L: 64 or 32
+    int32_t n;                 // coefficients; the rest of the last tile is padding
 };
 
 // Per-call arrays of one instance: theta [B x n_k], logL [B], info [B] or

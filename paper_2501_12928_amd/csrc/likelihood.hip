@@ -163,7 +163,7 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
 
             if (u0 == 0) {
                 __syncthreads();
-                const int f = tile_factor<S, NW>(sh.Dt, sh.dg, &sh.fail_sh);
+                const int f = tile_factor<S, NW>(sh.Dt, sh.dg, &sh.fail_sh, real_blocks<S>(uniform(I.n), j));
                 if (f) {
                     failed = j * S + f;
                     break;

@@ -200,7 +200,7 @@ constexpr int PT = 512;  // threads of the diagonal factorisation
 
 __global__ __launch_bounds__(PT) void ooc_potrf_kernel(const double2 *__restrict__ C0, double2 *__restrict__ Linv,
                                                         const double2 *__restrict__ w, double2 *__restrict__ y,
-                                                        int64_t j, OocState *st) {
+                                                        int64_t j, int64_t n, OocState *st) {
     __shared__ double2 D[OT * (OT + 1)];
     __shared__ double2 wj[OT];
     __shared__ double dg[OT], red[2][OT];
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(PT) void ooc_potrf_kernel(const double2 *__restrict
     }
     if (tid < OT) wj[tid] = w[OT * j + tid];
     __syncthreads();
-    const int f = tile_factor<OT, PT / 64>(D, dg, &fail);
+    const int f = tile_factor<OT, PT / 64>(D, dg, &fail, real_blocks<OT>(n, (int)j));
     if (f) {
         if (tid == 0) st->info = (int32_t)(OT * j + f);
         return;
@@ -619,7 +619,8 @@ extern "C" eor_status eor_loglike_host(int device, int64_t n, const double *A, i
             for (int64_t j = j0; j < j1; ++j) {
                 const int64_t rows = N - j;
                 double2 *Cj = L.C.p + (col_off(j) - col_off(j0)) * OT2;
-                hipLaunchKernelGGL(ooc_potrf_kernel, dim3(1), dim3(PT), 0, s, Cj, L.Linv.p, L.w.p, L.y.p, j, L.st.p);
+                hipLaunchKernelGGL(ooc_potrf_kernel, dim3(1), dim3(PT), 0, s, Cj, L.Linv.p, L.w.p, L.y.p, j, n,
+                                   L.st.p);
                 if (rows > 1)
                     hipLaunchKernelGGL(ooc_trsm_kernel, dim3((unsigned)(rows - 1)), dim3(BT), 0, s, Cj, L.Linv.p,
                                        L.w.p, L.y.p, j, L.st.p);

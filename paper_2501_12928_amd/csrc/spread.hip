@@ -312,9 +312,13 @@ __device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, 
     return true;
 }
 
-// Two workgroups per CU: four waves of 256 registers each, and while one waits
-// for a tile the other computes.
+// PER_CU workgroups of four waves per CU (spread_per_cu). Two: 256 registers a
+// wave, and while one waits for a tile the other computes. One, with
+// last_update: 256 registers as well, although a few spill there (with 512 the
+// accumulators moved between the two register files, 36 us a column against 31).
+template <int PER_CU>
 __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
+    constexpr bool hand = PER_CU == 1;
     __shared__ SpreadShared sh;
     const int w = uniform(threadIdx.x >> 6);
     // units before the current column, and its tile rows left
@@ -351,7 +355,6 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         const double2 *A = uniform_ptr(I.A);
         double2 *L = uniform_ptr(a.Lw + (a.off ? a.off[slot] : slot * a.slot_elems)), *yv = uniform_ptr(a.yw + slot * a.slot_y);
         int32_t *prog = uniform_ptr(a.prog + (int64_t)slot * (a.n_max + SPREAD_EXTRA));
-        const bool hand = a.per_cu == 1;
         d4 xr[4], xi[4];
         if (u <= 1) __builtin_amdgcn_s_setprio(2);
         if (u > 0) {
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                 ok = spread_sum(sh, A, L, prog, stop, i, j, j, w, t1, xr, xi);
                 spread_x(t1, xr, xi);
             }
-            if (ok && u == 1 && hand) {  // to the unit of diagonal tile i (last_update)
+            if (hand && ok && u == 1) {  // to the unit of diagonal tile i (last_update)
                 const int tid = opaque(threadIdx.x);
                 double2 *X = L + tile_index(i, i) * TS2 + tid;
 #pragma unroll
@@ -382,6 +385,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
             }
         } else {
             const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+            const int nb = real_blocks<TS>(uniform(I.n), j);
             const double *th = C.theta + bt * I.n_k;
             const int32_t bj = I.coef_bin[j * TS + 16 * w + l16];
             const double ivj = bj >= 0 ? 1.0 / (I.bin_scale[bj] * exp10(th[bj])) : I.coef_inv[j * TS + 16 * w + l16];
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
             if (ok) {
                 d4 t1[4];
                 ok = spread_sum(sh, A, L, prog, stop, j, j, hand && j > 0 ? j - 1 : j, w, t1, xr, xi);
-                if (ok && hand && j > 0) ok = last_update(sh, L, prog, stop, j, w, t1, xr, xi);
+                if (hand && ok && j > 0) ok = last_update(sh, L, prog, stop, j, w, t1, xr, xi);
                 spread_x(t1, xr, xi);
             }
             if (ok) {
@@ -415,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     }
                 }
                 __syncthreads();
-                const int f = tile_factor<TS, 4>(sh.Dt, sh.dg, &sh.fail);
+                const int f = tile_factor<TS, 4>(sh.Dt, sh.dg, &sh.fail, nb);
                 if (f) {
                     ok = false;
                     if (tid == 0) {
@@ -490,7 +494,10 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
 hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s) {
     const int64_t grid = std::min<int64_t>(p.units, (int64_t)p.per_cu * num_cu);
     if (grid < 1) return hipSuccess;
-    hipLaunchKernelGGL(spread_kernel, dim3((unsigned)grid), dim3(256), 0, s, p);
+    if (p.per_cu == 1)
+        hipLaunchKernelGGL(spread_kernel<1>, dim3((unsigned)grid), dim3(256), 0, s, p);
+    else
+        hipLaunchKernelGGL(spread_kernel<2>, dim3((unsigned)grid), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

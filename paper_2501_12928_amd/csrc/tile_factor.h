@@ -93,13 +93,23 @@ __device__ __forceinline__ void eliminate_all(Block16 &b, int l16, std::integer_
     (eliminate<C>(b, l16), ...);
 }
 
+// Blocks of 16 columns of tile j of side S that hold any of n columns.
+template <int S>
+__device__ inline int real_blocks(int64_t n, int j) {
+    const int64_t left = n - (int64_t)S * j;
+    return left >= S ? S / 16 : left <= 0 ? 0 : (int)((left + 15) / 16);
+}
+
 // D (S x S, column-major with leading dimension S + 1, both triangles valid)
 // becomes L^{-1} of its Cholesky factor L in its lower 16 x 16 blocks (the
 // blocks on the diagonal with exact zeros above theirs; the blocks above the
 // diagonal hold no result); dg receives the pivots L_cc^2. Called by all NW
 // waves (NW >= S / 16), after a barrier that follows the last write of D.
 // Returns 0, or the 1-based column of the first pivot that is not positive
-// and finite (the same value in every wave); ends with a barrier.
+// and finite (the same value in every wave); ends with a barrier. Only the
+// first nb <= S / 16 block columns are eliminated: what lies beyond has to be
+// the identity (the padding of a last tile), which is its own inverse: of the
+// 12.7 us below, 3.2 us per block left out.
 //
 // Bound by a serial chain: the S pivots in turn. Blocked on 16 x 16 blocks so
 // that the chain runs in one wave's registers: wave 0 eliminates the block on
@@ -118,12 +128,13 @@ __device__ __forceinline__ void eliminate_all(Block16 &b, int l16, std::integer_
 // one thread, took about 60 us more per tile: one theta at n = 200 444 -> 175
 // us, 256 at n = 2048 40.8 -> 39.3 ms.
 template <int S, int NW>
-__device__ __forceinline__ int tile_factor(double2 *D, double *dg, int *fail_sh) {
-    constexpr int NB = S / 16, LD = S + 1;
+__device__ __forceinline__ int tile_factor(double2 *D, double *dg, int *fail_sh, int nb) {
+    constexpr int LD = S + 1;
     const int tid = opaque(threadIdx.x);
     const int wv = uniform(tid >> 6), l16 = tid & 15, q = (tid >> 4) & 3;
+    if (tid >= 16 * nb && tid < S) dg[tid] = 1.0;
 #pragma unroll 1
-    for (int kb = 0; kb < NB; ++kb) {
+    for (int kb = 0; kb < nb; ++kb) {
         const int k0 = 16 * kb;
         // the row of the inverse that this wave forms: block (kb, jb)
         const int jb = wv - 1;
@@ -173,7 +184,7 @@ __device__ __forceinline__ int tile_factor(double2 *D, double *dg, int *fail_sh)
             __syncthreads();  // fail_sh is read by every wave before anything else is written
             return f;
         }
-        if (wv > kb && wv < NB) {
+        if (wv > kb && wv < nb) {
             // L_i,kb = D_i,kb V_kk^H, i = wv: lane holds [q + 4 r][l16]
             d4 t1 = d4{0, 0, 0, 0}, t2 = d4{0, 0, 0, 0}, t3 = d4{0, 0, 0, 0};
 #pragma unroll
@@ -208,7 +219,7 @@ __device__ __forceinline__ int tile_factor(double2 *D, double *dg, int *fail_sh)
         // Wave 0 takes only the next block on the diagonal and goes on to
         // eliminate it; the others' blocks and rows of the inverse are read
         // after the next barrier, or by the wave that stored them.
-        const int nblk = (NB - 1 - kb) * (NB - kb) / 2;
+        const int nblk = (nb - 1 - kb) * (nb - kb) / 2;
 #pragma unroll 1
         for (int idx = wv; idx < nblk; idx += wv == 0 ? nblk : NW - 1) {
             int i = 0;

@@ -38,3 +38,16 @@ def test_more_bins_than_the_table(orc, n_k):
     assert ok.tolist() == [True, False, True]
     got, ref = got[ok], ref[ok]
     assert np.all(np.abs(got - ref) <= np.minimum(tol(ref), 1e-10 * np.abs(ref)))
+
+
+@pytest.mark.parametrize("ts", [64, 32])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 48, 49, 63, 64, 65, 97, 112, 113])
+def test_padded_blocks_are_left_out(orc, n, ts):
+    """The 16-wide blocks of the last tile that hold only padding are not
+    eliminated: 0 (a whole 32-wide tile of padding) to 4 of them."""
+    inst = synth.small(seed=93, m=2 * n + 20, n=n, n_k=1, n_theta=3)
+    ref, rinfo = orc.loglike_instance(inst)
+    print(f"gpu: n={n} tile {ts}", flush=True)
+    got, info = run_instance(inst, ts=ts)
+    np.testing.assert_array_equal(info, rinfo)
+    assert np.all(np.abs(got - ref) <= np.minimum(tol(ref), 1e-10 * np.abs(ref)))
