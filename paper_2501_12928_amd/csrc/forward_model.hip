@@ -16,11 +16,8 @@
 //    products per complex step (Gauss). The pixel sum is cut into chunks so
 //    that there are several workgroups per resident slot (the chip then
 //    stays evenly loaded to the end); each chunk's sum goes to its own
-//    partial of G. While the matrix cores work on one stage of 16 pixels,
-//    the loads of the next stage's S rows, pixel directions and beam values
-//    are in flight. Two workgroups share a CU (the register budget is bounded
-//    for it), so one makes its phase factors and fills LDS while the other's
-//    products run.
+//    partial of G. Two workgroups share a CU (the register budget is bounded
+//    for it).
 //  - fm_expand_kernel: adds the partials in chunk order and writes T, one
 //    thread per (row, uv cell) and all the spectral modes, so that T is
 //    written once, in full rows (non-temporal stores: it is not read here).
@@ -37,7 +34,8 @@ namespace {
 constexpr double C_LIGHT = 299792458.0;  // m / s
 constexpr int FB = 32;                   // tile: 32 baselines ...
 constexpr int FU = 128;                  // ... x 128 uv cells
-constexpr int FK = 16;                   // pixels per stage
+constexpr int FK = 32;                   // pixels per stage of phase factors
+constexpr int FC = 16;                   // pixels: granularity of the chunks
 
 __device__ inline d4 mfma64(double a, double b, d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -58,72 +56,90 @@ __global__ void sky_modes_kernel(const double *__restrict__ lm, const double *__
 struct FmArgs {
     const double *freq, *bl, *lm, *beam;
     const double2 *S;  // [n_pix][n_uv]
-    int64_t n_pix, chunk;  // pixels; pixels per chunk (a multiple of FK)
+    int64_t n_pix, chunk;  // pixels; pixels per chunk (a multiple of FC)
     int n_freq, n_bl, n_uv, nbt, n_chunk;
     double2 *G;  // partials [n_chunk][n_freq n_bl][n_uv]
 };
 
-// A thread's staging values: eight S entries of one pixel row (held as a
-// register vector rather than an array), and the directions and beam values
-// of two pixels, from which their phase factors are made.
-typedef double d16 __attribute__((ext_vector_type(16)));
-struct SRow {
-    d16 v;  // entry i: (re, im) at 2 i, 2 i + 1
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+
+// S at four pixels from p (uniform) and the lane's four columns: lane group q
+// takes pixel p + q; zero past the last pixel. The descriptor covers the rows
+// of S that exist, so the prefetch past a chunk's end needs no guard.
+struct SStep {
+    double2 v[4];
 };
+
+__device__ __forceinline__ void load_s(const FmArgs &a, SStep &x, int64_t p, const int voff[4]) {
+    const int64_t left = a.n_pix - p;
+    const rsrc_t R = __builtin_amdgcn_make_buffer_rsrc(const_cast<double2 *>(a.S + (left <= 0 ? 0 : p * a.n_uv)), (short)0,
+                                                       (int)((left <= 0 ? 0 : left < 4 ? left : 4) * a.n_uv * 16), 0x00020000);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const u4 t = __builtin_amdgcn_raw_buffer_load_b128(R, voff[c], 0, 0);
+        __builtin_memcpy(&x.v[c], &t, 16);
+    }
+}
+
+// Direction and beam value of a pixel, from which a phase factor is made.
 struct Pix {
-    double2 lm[2];
-    double beam[2];
+    double2 lm;
+    double beam;
 };
 
-// S row p0 + sp at columns k0 + sk + 16 i (both clamped to the last one).
-__device__ __forceinline__ void load_s(const FmArgs &a, SRow &r, int64_t p0, int sp, int sk, int k0,
-                                       int64_t klast) {
-    const double2 *Srow = a.S + min(p0 + sp, a.n_pix - 1) * a.n_uv;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const double2 v = Srow[min<int64_t>(k0 + sk + 16 * i, klast)];
-        r.v[2 * i] = v.x;
-        r.v[2 * i + 1] = v.y;
-    }
+// Pixel p, clamped to the last one.
+__device__ __forceinline__ Pix load_pix(const FmArgs &a, int64_t p, const double2 *lm2, const double *beam) {
+    const int64_t pc = min(p, a.n_pix - 1);
+    return Pix{lm2[pc], beam[pc]};
 }
 
-// Pixels p0 + ep and p0 + ep + 1: direction (clamped to the last pixel) and
-// beam value (zero past the chunk's end).
-__device__ __forceinline__ void load_pix(const FmArgs &a, Pix &x, int64_t p0, int64_t pend, int ep,
-                                         const double2 *lm2, const double *beam) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int64_t p = p0 + ep + j, pc = min(p, a.n_pix - 1);
-        x.lm[j] = lm2[pc];
-        const double bv = beam[pc];  // in bounds: pc is clamped
-        x.beam[j] = p < pend ? bv : 0.0;
-    }
+// exp(2 pi i v) from the table of exp(2 pi i k / TURN): with k the nearest of
+// the TURN directions, cos and sin of what is left (at most pi / TURN = 0.0123)
+// by their Taylor polynomials, whose first terms left out are below 1e-17. The
+// product is added to the table's value last, so that its error is one rounding
+// beside the table's own. The reduction to |f| <= 1/2 is exact for every v.
+// About 25 instructions against sincospi's 75, which cost SIMD time of the matrix
+// cores (vector instructions do not run beside another wave's FP64 MFMA): 1.11
+// against 1.15 ms for 20000 x 4096. T against 80-bit arithmetic: rms 4.8e-16 to
+// 6.6e-16 over four instruments, with sincospi 5.0e-16 to 8.0e-16.
+constexpr int TURN = 256;
+
+__device__ __forceinline__ double2 cis_turns(double v, const double2 *turn) {
+    const double f = v - rint(v), t = f * TURN, kd = rint(t);
+    const double2 e = turn[(int)kd & (TURN - 1)];
+    const double r = (t - kd) * (6.283185307179586476925 / TURN), r2 = r * r;
+    const double sr = fma(r * r2, fma(r2, 1.0 / 120.0, -1.0 / 6.0), r);
+    const double cm = r2 * fma(r2, fma(r2, -1.0 / 720.0, 1.0 / 24.0), -0.5);  // cos r - 1
+    return make_double2(e.x + fma(-e.y, sr, e.x * cm), e.y + fma(e.x, sr, e.y * cm));
 }
 
-// E for one baseline at the two pixels: A exp(-2 pi i nu / c (x l + y m)).
-__device__ __forceinline__ void phases(const Pix &x, double fc, double bx, double by, double2 e[2]) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        double s, c;
-        sincospi(-2.0 * fc * (bx * x.lm[j].x + by * x.lm[j].y), &s, &c);
-        e[j] = make_double2(x.beam[j] * c, x.beam[j] * s);
-    }
+// E for one baseline at the pixel: A exp(-2 pi i nu / c (x l + y m)), with A =
+// 0 past the chunk's end.
+__device__ __forceinline__ double2 phase(const Pix &x, bool in, double fc, double bx, double by, const double2 *turn) {
+    const double2 u = cis_turns(-fc * (bx * x.lm.x + by * x.lm.y), turn);
+    const double beam = in ? x.beam : 0.0;
+    return make_double2(beam * u.x, beam * u.y);
 }
 
 // One workgroup per (uv tile, chunk, channel, baseline tile), baseline tile
 // fastest. Wave w owns tile rows (baselines) 16 (w % 2) .. + 15 and uv
-// columns 64 (w / 2) .. + 63, as four 16-column blocks. Staging: thread t
-// makes the phases of baseline t / 8 at pixels 2 (t % 8) and 2 (t % 8) + 1,
-// and copies S row t / 16 at columns t % 16 + 16 i, i = 0 .. 7. Indices past
-// the last baseline, pixel row or uv cell are clamped to the last one (those
-// rows and columns are never written); pixels past the chunk get a beam
-// value of zero, so they add nothing.
-// At most 256 registers per lane (two workgroups per CU): the accumulators
-// then live in ordinary vector registers, with no copies to and from the
-// accumulation registers at every stage.
+// columns 64 (w / 2) .. + 63, as four 16-column blocks. Indices past the last
+// baseline or uv cell are clamped to the last one (those rows and columns are
+// never written); pixels past the chunk get a beam value of zero and pixels past
+// the last a row of zeros of S, so they add nothing.
+// S goes from L2 straight to the operand registers, three steps ahead; only the
+// phase factors, which are made once for all waves, pass through LDS, in stages
+// of 32 pixels with one barrier each. (With both staged through LDS, 16 pixels
+// and two barriers a stage, the waves of a workgroup held each other up: matrix
+// cores busy 69% of the time, 1.19 ms for 20000 x 4096. Now 84%, 1.11 ms; at the
+// clock it runs at, 2.1 GHz, the products alone take 0.94 ms. Two LDS buffers of
+// 8 pixels instead gave 1.18.) At most 256 registers per lane (two workgroups
+// per CU): the accumulators then live in ordinary vector registers, with no
+// copies to and from the accumulation registers.
 __global__ __launch_bounds__(256, 2) void fm_partial_kernel(FmArgs a) {
-    __shared__ double2 Es[FB][FK + 1];  // [baseline][pixel]
-    __shared__ double2 Bs[FK][FU + 1];  // [pixel][uv cell]
+    __shared__ double2 Es[2][FB][FK + 1];  // [baseline][pixel]
+    __shared__ double2 turn[TURN];         // exp(2 pi i k / TURN)
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q = lane >> 4;
     const int wr = 16 * (w & 1), wc = 64 * (w >> 1);
     int64_t u = blockIdx.x;
@@ -138,57 +154,66 @@ __global__ __launch_bounds__(256, 2) void fm_partial_kernel(FmArgs a) {
     const double fc = a.freq[f] / C_LIGHT;
     const double *beam = a.beam + (int64_t)f * a.n_pix;
     const double2 *lm2 = reinterpret_cast<const double2 *>(a.lm);
-    // this thread's staging roles
-    const int eb = tid >> 3, ep = 2 * (tid & 7);
+    // this thread's phase factors: baseline eb, pixels ep + 8 i of a stage
+    const int eb = tid >> 3, ep = tid & 7;
     const int be = min(b0 + eb, a.n_bl - 1);
     const double bx = a.bl[2 * be], by = a.bl[2 * be + 1];
-    const int sp = tid >> 4, sk = tid & 15;
-    const int64_t klast = a.n_uv - 1;
+    int voff[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) voff[c] = (q * a.n_uv + min(k0 + wc + 16 * c + l16, a.n_uv - 1)) * 16;
 
-    // Pipeline: while the products of stage s run, stage s + 1's S row is in
-    // flight, its phase factors are made from the pixel values loaded during
-    // stage s - 1, and the pixel values of stage s + 2 are loaded. The loads
-    // past the chunk's end are clamped and their results never stored.
-    SRow sn;
-    Pix xc, xn;
-    double2 en[2];
+    // Pipeline: S three steps of four pixels ahead; while the products of stage
+    // s run, the phase factors of stage s + 1 are made, one between every two
+    // steps, from pixel values loaded during stage s - 1, and go to the other LDS
+    // buffer, and the pixel values of stage s + 2 are loaded.
+    constexpr int NP = FK / 8, AHEAD = 3;
+    SStep sb[AHEAD + 1];
+    Pix x[NP];
     d4 t1[4], t2[4], t3[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) t1[c] = t2[c] = t3[c] = d4{0.0, 0.0, 0.0, 0.0};
-    load_s(a, sn, pbeg, sp, sk, k0, klast);
-    load_pix(a, xc, pbeg, pend, ep, lm2, beam);
-    phases(xc, fc, bx, by, en);
-    load_pix(a, xc, pbeg + FK, pend, ep, lm2, beam);
-    Es[eb][ep] = en[0];
-    Es[eb][ep + 1] = en[1];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) Bs[sp][sk + 16 * i] = make_double2(sn.v[2 * i], sn.v[2 * i + 1]);
+    for (int i = 0; i < NP; ++i) x[i] = load_pix(a, pbeg + ep + 8 * i, lm2, beam);
+    {
+        static_assert(TURN == 256, "one entry per thread");
+        double sn, cs;
+        sincospi(tid * (2.0 / TURN), &sn, &cs);
+        turn[tid] = make_double2(cs, sn);
+    }
     __syncthreads();
-    const int ns = (int)((pend - pbeg + FK - 1) / FK);  // stages of this chunk
-    for (int it = 0; it < ns; ++it) {
-        const int64_t p0 = pbeg + (int64_t)it * FK;
-        load_s(a, sn, p0 + FK, sp, sk, k0, klast);
-        load_pix(a, xn, p0 + 2 * FK, pend, ep, lm2, beam);
-        phases(xc, fc, bx, by, en);
 #pragma unroll
-        for (int ks = 0; ks < FK; ks += 4) {
-            const double2 av = Es[wr + l16][ks + q];
+    for (int i = 0; i < NP; ++i) {
+        Es[0][eb][ep + 8 * i] = phase(x[i], pbeg + ep + 8 * i < pend, fc, bx, by, turn);
+        x[i] = load_pix(a, pbeg + FK + ep + 8 * i, lm2, beam);
+    }
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+        load_s(a, sb[u], pbeg + 4 * u, voff);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    int buf = 0;
+#pragma unroll 1
+    for (int64_t p0 = pbeg; p0 < pend; p0 += FK, buf ^= 1) {
+#pragma unroll
+        for (int u = 0; u < FK / 4; ++u) {
+            load_s(a, sb[(u + AHEAD) % (AHEAD + 1)], p0 + 4 * (u + AHEAD), voff);
+            __builtin_amdgcn_sched_barrier(0);
+            const double2 av = Es[buf][wr + l16][4 * u + q];
             const double as = av.x + av.y;
+            const SStep &s = sb[u % (AHEAD + 1)];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const double2 bv = Bs[ks + q][wc + 16 * c + l16];
-                t1[c] = mfma64(av.x, bv.x, t1[c]);
-                t2[c] = mfma64(av.y, bv.y, t2[c]);
-                t3[c] = mfma64(as, bv.x + bv.y, t3[c]);
+                t1[c] = mfma64(av.x, s.v[c].x, t1[c]);
+                t2[c] = mfma64(av.y, s.v[c].y, t2[c]);
+                t3[c] = mfma64(as, s.v[c].x + s.v[c].y, t3[c]);
             }
-        }
-        __syncthreads();
-        if (it + 1 < ns) {  // uniform
-            Es[eb][ep] = en[0];
-            Es[eb][ep + 1] = en[1];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) Bs[sp][sk + 16 * i] = make_double2(sn.v[2 * i], sn.v[2 * i + 1]);
-            xc = xn;
+            if (u % 2 == 1) {
+                const int64_t p = p0 + FK + ep + 4 * (u - 1);
+                Es[buf ^ 1][eb][ep + 4 * (u - 1)] = phase(x[u / 2], p < pend, fc, bx, by, turn);
+                x[u / 2] = load_pix(a, p + FK, lm2, beam);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
     }
@@ -265,10 +290,10 @@ extern "C" eor_status eor_forward_model(int64_t n_freq, int64_t n_bl, int64_t n_
     // Pixel chunks: enough workgroups for several per resident slot (about
     // 2048 in all), at most 16 chunks and at least one stage per chunk.
     const int64_t nbt = (n_bl + eor::FB - 1) / eor::FB, nut = (n_uv + eor::FU - 1) / eor::FU;
-    const int64_t base = n_freq * nbt * nut, stages = (n_pix + eor::FK - 1) / eor::FK;
+    const int64_t base = n_freq * nbt * nut, stages = (n_pix + eor::FC - 1) / eor::FC;
     int64_t want = (2048 + base - 1) / base;
     want = std::max<int64_t>(1, std::min<int64_t>({want, 16, stages}));
-    const int64_t chunk = ((stages + want - 1) / want) * eor::FK;
+    const int64_t chunk = ((stages + want - 1) / want) * eor::FC;
     const int64_t n_chunk = (n_pix + chunk - 1) / chunk;
     const int64_t units = base * n_chunk, rows = n_freq * n_bl;
     if (units > (int64_t)INT32_MAX)

@@ -44,6 +44,22 @@ def test_forward_model_matches_oracle(F, n_bl, n_pix, n_uv, n_eta):
     assert np.all(np.isnan(got[:, n_eta * n_uv:]))
 
 
+@pytest.mark.parametrize("n_pix", [1, 3, 4, 5, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 65, 129, 511, 513])
+def test_forward_model_pixel_counts(n_pix):
+    """Pixel counts around the four-pixel steps, the 16-pixel grain of the
+    chunks and the 32-pixel stages. A phase of at most 12 turns carries a few
+    roundings, 1e-13 of E, in the kernel and in the oracle; the pixel sum is
+    bounded by all terms in phase."""
+    import torch
+    import paper_2501_12928_amd as eor
+    rng = np.random.default_rng(n_pix)
+    freq, bl, lm, beam, uv, Z = _random_instrument(rng, 2, 33, n_pix, 17, 2)
+    ref = fm.forward_model(freq, bl, lm, beam, uv, Z, 1.0)
+    print(f"gpu: forward model n_pix={n_pix}", flush=True)
+    got = eor.forward_model(freq, bl, lm, beam, uv, Z, 1.0).cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= 1e-13 * n_pix * beam.max() * np.abs(Z).max()
+
+
 def test_forward_model_full_instrument_sampled():
     """The 20000 x 4096 synthetic instrument (32 channels, 625 baselines,
     64 x 64 pixels, 128 uv cells, 4 foreground + 28 EoR spectral modes):
