@@ -9,8 +9,8 @@ namespace eor {
 // Words of one theta's progress row beside the N counts of finished tiles:
 // stop (the theta has failed), tails (diagonal tiles whose ln d is stored),
 // done (finished units), handed (the last row whose X is in its diagonal
-// tile's slot).
-constexpr int SPREAD_EXTRA = 4;
+// tile's slot), inverses (diagonal tiles whose inverse is stored).
+constexpr int SPREAD_EXTRA = 5;
 
 struct SpreadParams {
     const InstDesc *inst;    // device [n_inst]

@@ -34,11 +34,12 @@
 // Tile (j+1, j) would be formed, announced and read back between the two;
 // instead its unit hands over X (what Linv_jj is still to be applied to) while
 // tile (j, j) is being factored, and the unit of tile (j+1, j+1) forms L_(j+1)j
-// itself and updates from LDS (last_update): 37 -> 31 us per column (factor 14.4,
-// y and stores 2, announced, seen and loaded 3, tile below 4.4, update and move
-// to LDS 7). With one workgroup per CU (spread_per_cu) one theta at n = 4096 takes
-// 1.93 ms (253 by one workgroup, 2.46 with tile (j+1, j) read back and two per CU),
-// at n = 2048 0.95 (33.5, 1.12), at n = 200 130 us (190, 134). With many theta
+// itself and updates from LDS (last_update): 37 -> 31 us per column, and Linv_jj
+// is announced by itself, before y_j: 29.5 us (factor 14.4, stored and announced
+// 2, seen and loaded 2.3, tile below 4.3, update and move to LDS 6.5). With one
+// workgroup per CU (spread_per_cu) one theta at n = 4096 takes 1.89 ms (253 by
+// one workgroup, 2.46 with tile (j+1, j) read back and two per CU), at n = 2048
+// 0.91 (33.5, 1.12), at n = 200 114 us (190, 134). With many theta
 // the FP64 matrix cores and the panels' traffic (each unit streams both of its
 // panels alone) bound: 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79
 // with 256 theta of one workgroup each, where two tiles share a panel; so full
@@ -267,7 +268,7 @@ __device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, 
             xr[cb][r] = v.x;
             xi[cb][r] = v.y;
         }
-    if (wait_tiles(prog, stop, j - 1, j - 1, j - 1, 0, &sh.seen) < 0) return false;
+    if (wait_tiles(prog, stop, stop + 4, stop + 4, j - 1, 0, &sh.seen) < 0) return false;
     load_linv(sh, L, j - 1, tid);
     __syncthreads();
     // Y = X Linv^H as in tile_below, last column block first: it alone needs all of X
@@ -428,6 +429,21 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     }
                 }
             }
+            auto store_linv = [&](int tid) {
+                double2 *V = L + tile_index(j, j) * TS2;
+#pragma unroll
+                for (int b = 0; b < 10; ++b) {
+                    int r, c;
+                    lower_block(b, tid, r, c);
+                    const double2 v = sh.Dt[c * (TS + 1) + r];
+                    std2(V + c * TS + r, v.x, v.y);
+                }
+            };
+            // to the next diagonal tile, which needs no y_j: 1.4 us earlier
+            if (hand && ok && j < N - 1) {
+                store_linv(opaque(threadIdx.x));
+                publish(prog + stop + 4, j + 1);
+            }
             // w_j, which tile (j, j - 1) completes beside the factorisation
             if (ok && j > 0) ok = wait_tiles(prog, stop, j, j, j - 1, 0, &sh.seen) >= 0;
             if (ok) {
@@ -438,14 +454,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                 const double2 y = tile_solve<TS>(sh.Dt, sh.wv, w, l16, q);
                 if (q == 0) std2(yv + j * TS + row, y.x, y.y);
                 if (j < N - 1) {
-                    double2 *V = L + tile_index(j, j) * TS2;
-#pragma unroll
-                    for (int b = 0; b < 10; ++b) {
-                        int r, c;
-                        lower_block(b, tid, r, c);
-                        const double2 v = sh.Dt[c * (TS + 1) + r];
-                        std2(V + c * TS + r, v.x, v.y);
-                    }
+                    if (!hand) store_linv(tid);
                     publish(prog + j, j + 1);
                     // beside the chain of diagonal tiles: the column's ln d
                     if (q == 1) *lnd_of(L, j, row) = log(sh.dg[row]);
@@ -459,9 +468,11 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     wait_tiles(prog, stop, a.n_max + 1, a.n_max + 1, N - 2, 0, &sh.seen);  // every ln d
                     double acc = 0.0;
                     if (q == 0) {
+#pragma unroll 8
                         for (int c = 0; c < N - 1; ++c) acc += abs2(ldd2(yv + c * TS + row));
                         acc += abs2(y);
                     } else if (q == 1) {
+#pragma unroll 8
                         for (int c = 0; c < N - 1; ++c) acc += ldg(lnd_of(L, c, row));
                         acc += log(sh.dg[row]);
                     }
