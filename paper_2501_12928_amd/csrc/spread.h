@@ -38,12 +38,12 @@ hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s);
 //  - one workgroup takes a theta of N tile rows in 30 N + 1.5 N^2 + 0.93 N^3
 //    (200 us at n = 200, 4.7 ms at 1003, 253 ms at 4096), up to 15% more when
 //    all workgroups run;
-//  - spread, a theta's diagonal tiles follow one another every 30 us, and its
+//  - spread, a theta's diagonal tiles follow one another every 27 us, and its
 //    N (N + 1) / 2 tiles take the whole GPU 0.08 us each plus their products at
 //    78 TFLOP/s. The chain and the work of all theta overlap almost wholly where
 //    the chain is the longer, in part otherwise.
 inline double lone_us(int64_t N) { return 30.0 * N + 1.5 * N * N + 0.93 * N * N * N; }
-inline double spread_chain_us(int64_t N) { return 30.0 * N; }
+inline double spread_chain_us(int64_t N) { return 27.0 * N; }
 inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 * 262144.0 * N * N * N / 78e6; }
 inline double spread_us(double chain, double work) {
     return chain > work ? chain + 0.1 * work : work + 0.3 * chain;

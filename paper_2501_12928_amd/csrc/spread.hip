@@ -34,17 +34,18 @@
 // Tile (j+1, j) would be formed, announced and read back between the two;
 // instead its unit hands over X (what Linv_jj is still to be applied to) while
 // tile (j, j) is being factored, and the unit of tile (j+1, j+1) forms L_(j+1)j
-// itself and updates from LDS (last_update): 37 -> 31 us per column, and Linv_jj
-// is announced by itself, before y_j: 29.5 us (factor 14.4, stored and announced
-// 2, seen and loaded 2.3, tile below 4.3, update and move to LDS 6.5). With one
-// workgroup per CU (spread_per_cu) one theta at n = 4096 takes 1.89 ms (253 by
-// one workgroup, 2.46 with tile (j+1, j) read back and two per CU), at n = 2048
-// 0.91 (33.5, 1.12), at n = 200 114 us (190, 134). With many theta
+// itself and updates from LDS (last_update): 37 -> 31 us per column; Linv_jj is
+// announced by itself, before y_j: 29.5; and a diagonal tile is formed only in
+// its lower triangle (DiagBlocks): 27 us (factor 14.4, stored and announced 2,
+// seen and loaded 2.3, tile below 4.3, update and move to LDS 4). With one
+// workgroup per CU (spread_per_cu) one theta at n = 4096 takes 1.72 ms (253 by
+// one workgroup, 2.46 before these three and with two per CU), at n = 2048 0.85
+// (33.5, 1.12), at n = 200 109 us (190, 134). With many theta
 // the FP64 matrix cores and the panels' traffic (each unit streams both of its
 // panels alone) bound: 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79
 // with 256 theta of one workgroup each, where two tiles share a panel; so full
 // rounds stay there (spread_count in abi.hip, build_spread in runtime.hip). There
-// nothing is handed over: with it 24 theta at n = 1003 took 800 us, 784 without.
+// nothing is handed over: with it 64 theta at n = 1003 took 1.89 ms, 1.75 without.
 #include <algorithm>
 
 #include "like_device.h"
@@ -164,6 +165,23 @@ __device__ __forceinline__ void accumulate(rsrc_t P, rsrc_t Q, int k0, int k1, i
     } while (c < end);
 }
 
+// sum(k, e) over the tiles k .. e - 1 of rows i and j that have finished, until
+// kend; false if the theta has failed.
+template <class F>
+__device__ __forceinline__ bool as_they_finish(SpreadShared &sh, const int32_t *prog, int stop, int i, int j, int kend,
+                                               F &&sum) {
+    int k = 0;
+#pragma unroll 1
+    while (k < kend) {
+        const int v = wait_tiles(prog, stop, i, j, k, i <= j + 1 ? j - k - 1 : j - k, &sh.seen);
+        if (v < 0) return false;
+        const int e = min(v, kend);
+        sum(k, e);
+        k = e;
+    }
+    return true;
+}
+
 // Accumulators of X = A_ij - sum_{k < kend} L_ik L_jk^H as the tiles finish
 // (kend <= j), in tile_update's form: t1, xr = T2, t3; false if the theta has
 // failed.
@@ -190,26 +208,102 @@ __device__ __forceinline__ bool spread_sum(SpreadShared &sh, const double2 *A, c
     }
     const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * TS2 + 16 * w, (int64_t)kend * TS * COLB);
     const rsrc_t Qr = make_rsrc(L + tile_index(j, 0) * TS2, (int64_t)kend * TS * COLB);
-    bool ok = true;
-    if (kend > 0) {
-        int k = 0;
-#pragma unroll 1
-        do {
-            const int v = wait_tiles(prog, stop, i, j, k, i <= j + 1 ? j - k - 1 : j - k, &sh.seen);
-            ok = v >= 0;
-            if (!ok) break;
-            const int e = min(v, kend);
-            accumulate(Pr, Qr, k, e, voff, t1, xr, t3);
-            k = e;
-        } while (k < kend);
+    return as_they_finish(sh, prog, stop, i, j, kend,
+                          [&](int k, int e) { accumulate(Pr, Qr, k, e, voff, t1, xr, t3); });
+}
+
+// The 16 x 16 blocks of a diagonal tile that wave w forms: of the ten in the
+// lower triangle (the factorisation reads no others) three each, one the last
+// wave, in place of four each with six above the diagonal: the last update, which
+// is part of the chain, takes 9 instead of 12 products a step. Block b lies in
+// rows 16 r(b), columns 16 c(b): (x1, x0), (x1, x1), (p2, q2); the last wave's
+// second and third are not used.
+struct DiagBlocks {
+    int x0, x1, p2, q2;
+    __device__ DiagBlocks(int w) : x0(w == 3 ? 2 : 0), x1(w == 0 ? 1 : w == 1 ? 2 : 3), p2(w == 0 ? 0 : x1), q2(w == 0 ? 0 : 1) {}
+    __device__ int r(int b) const { return b < 2 ? x1 : p2; }
+    __device__ int c(int b) const { return b == 0 ? x0 : b == 1 ? x1 : q2; }
+};
+
+// Rows 16 x + l16 of one step of the panel, for the four slabs of DiagBlocks.
+struct DiagStep {
+    double2 x0, x1, p2, q2;
+};
+
+__device__ __forceinline__ void mma_diag(const DiagStep &s, d4 t1[3], d4 t2[3], d4 t3[3]) {
+    auto block = [&](int b, double2 p, double2 q) {
+        t1[b] = mfma64(q.x, p.x, t1[b]);
+        t2[b] = mfma64(q.y, p.y, t2[b]);
+        t3[b] = mfma64(q.x - q.y, p.x + p.y, t3[b]);
+    };
+    block(0, s.x1, s.x0);
+    block(1, s.x1, s.x1);
+    block(2, s.p2, s.q2);
+}
+
+// accumulate for a diagonal tile: P = Q, the blocks of DiagBlocks.
+__device__ __forceinline__ void accumulate_diag(rsrc_t Q, int k0, int k1, int voff, const DiagBlocks &B, d4 t1[3],
+                                                d4 t2[3], d4 t3[3]) {
+    const int beg = k0 * TS, end = k1 * TS;
+    auto load = [&](DiagStep &s, int col) {
+        s.x0 = ld2(Q, voff, col * COLB + 256 * B.x0);
+        s.x1 = ld2(Q, voff, col * COLB + 256 * B.x1);
+        s.p2 = ld2(Q, voff, col * COLB + 256 * B.p2);
+        s.q2 = ld2(Q, voff, col * COLB + 256 * B.q2);
+    };
+    DiagStep buf[STAGES];
+#pragma unroll
+    for (int s0 = 0; s0 < STAGES - 1; ++s0) {
+        load(buf[s0], beg + 4 * s0);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    return ok;
+    int c = beg;  // end > beg
+#pragma unroll 1
+    do {
+        if ((c & (ALIGN_COLS - 1)) == 0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < STAGES; ++u) {
+            load(buf[(u + STAGES - 1) % STAGES], min(c + 4 * (u + STAGES - 1), end - 4));
+            __builtin_amdgcn_sched_barrier(0);
+            mma_diag(buf[u], t1, t2, t3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        c += 4 * STAGES;
+    } while (c < end);
+}
+
+// spread_sum for diagonal tile j.
+__device__ __forceinline__ bool spread_sum_diag(SpreadShared &sh, const double2 *A, const double2 *L,
+                                                const int32_t *prog, int stop, int j, int kend, const DiagBlocks &B,
+                                                d4 t1[3], d4 xr[3], d4 t3[3]) {
+    const int lane = opaque(threadIdx.x & 63), l16 = lane & 15, q = lane >> 4;
+    const rsrc_t Ar = make_rsrc(A + tile_index(j, j) * TS2, (int64_t)TS2 * 16);
+    const int voff = (q * TS + l16) * 16;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int so = (16 * B.c(b) + 4 * r) * A_COL_BYTES + 256 * B.r(b);
+            xr[b][r] = ld1(Ar, voff, so);
+            t3[b][r] = ld1(Ar, voff + 8, so);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        t1[b] = d4{0, 0, 0, 0};
+        t3[b] = xr[b] - t3[b];
+        xr[b] = -xr[b];
+    }
+    const rsrc_t Qr = make_rsrc(L + tile_index(j, 0) * TS2, (int64_t)kend * TS * COLB);
+    return as_they_finish(sh, prog, stop, j, j, kend,
+                          [&](int k, int e) { accumulate_diag(Qr, k, e, voff, B, t1, xr, t3); });
 }
 
 // X from its accumulators: real part into xr = T2, imaginary part into t3.
-__device__ __forceinline__ void spread_x(const d4 t1[4], d4 xr[4], d4 t3[4]) {
+template <int NB>
+__device__ __forceinline__ void spread_x(const d4 *t1, d4 *xr, d4 *t3) {
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
+    for (int cb = 0; cb < NB; ++cb) {
         const d4 a = t1[cb], b = xr[cb];
         xr[cb] = -(a + b);
         t3[cb] = a - b - t3[cb];
@@ -254,7 +348,7 @@ __device__ __forceinline__ void load_linv(SpreadShared &sh, const double2 *L, in
 // update nothing passes between workgroups. t1, t2, t3 += L_jk L_jk^H. False if
 // the theta has failed.
 __device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, const int32_t *prog, int stop, int j,
-                                            int w, d4 t1[4], d4 t2[4], d4 t3[4]) {
+                                            const DiagBlocks &B, int w, d4 t1[3], d4 t2[3], d4 t3[3]) {
     constexpr int LD = TS + 1;
     if (wait_tiles(prog, stop, stop + 3, stop + 3, j - 1, 1, &sh.seen) < 0) return false;
     const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
@@ -302,12 +396,8 @@ __device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, 
     __syncthreads();
 #pragma unroll 2
     for (int c = 0; c < TS; c += 4) {
-        Step<4> s;
         const double2 *col = sh.Dt + (c + q) * LD + l16;
-        s.p = col[16 * w];
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) s.qv[cb] = col[16 * cb];
-        mma_step(s, t1, t2, t3);
+        mma_diag(DiagStep{col[16 * B.x0], col[16 * B.x1], col[16 * B.p2], col[16 * B.q2]}, t1, t2, t3);
     }
     __syncthreads();
     return true;
@@ -363,7 +453,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
             {
                 d4 t1[4];
                 ok = spread_sum(sh, A, L, prog, stop, i, j, j, w, t1, xr, xi);
-                spread_x(t1, xr, xi);
+                spread_x<4>(t1, xr, xi);
             }
             if (hand && ok && u == 1) {  // to the unit of diagonal tile i (last_update)
                 const int tid = opaque(threadIdx.x);
@@ -385,11 +475,17 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                 publish(prog + i, j + 1);
             }
         } else {
-            const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
+            const int tid = opaque(threadIdx.x), l16 = tid & 15;
             const int nb = real_blocks<TS>(uniform(I.n), j);
             const double *th = C.theta + bt * I.n_k;
-            const int32_t bj = I.coef_bin[j * TS + 16 * w + l16];
-            const double ivj = bj >= 0 ? 1.0 / (I.bin_scale[bj] * exp10(th[bj])) : I.coef_inv[j * TS + 16 * w + l16];
+            double iv[3];  // 1 / phi of the rows of blocks on the diagonal
+#pragma unroll
+            for (int b = 1; b < 3; ++b) {
+                const int row = j * TS + 16 * (b == 1 ? DiagBlocks(w).x1 : 0) + l16;
+                const int32_t bj = I.coef_bin[row];
+                iv[b] = bj >= 0 ? 1.0 / (I.bin_scale[bj] * exp10(th[bj])) : I.coef_inv[row];
+            }
+            iv[0] = 0.0;
             // the theta's check comes with its first unit, ln det Phi with its last
             double ldp = 0.0;
             bool ok = true;
@@ -401,22 +497,24 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
                     store_word(prog + stop, 1);
                 }
             }
+            const DiagBlocks B(w);
             if (ok) {
-                d4 t1[4];
-                ok = spread_sum(sh, A, L, prog, stop, j, j, hand && j > 0 ? j - 1 : j, w, t1, xr, xi);
-                if (hand && ok && j > 0) ok = last_update(sh, L, prog, stop, j, w, t1, xr, xi);
-                spread_x(t1, xr, xi);
+                d4 t1[3];
+                ok = spread_sum_diag(sh, A, L, prog, stop, j, hand && j > 0 ? j - 1 : j, B, t1, xr, xi);
+                if (hand && ok && j > 0) ok = last_update(sh, L, prog, stop, j, B, w, t1, xr, xi);
+                spread_x<3>(t1, xr, xi);
             }
             if (ok) {
                 const int tid = opaque(threadIdx.x), l16 = tid & 15, q = (tid >> 4) & 3;
-                const int lo = q * (TS + 1) + 16 * w + l16;  // [16w + l16][q]
 #pragma unroll
-                for (int cb = 0; cb < 4; ++cb) {
+                for (int b = 0; b < 3; ++b) {
+                    if (w == 3 && b > 0) break;
+                    const int lo = (16 * B.c(b) + q) * (TS + 1) + 16 * B.r(b) + l16;  // [16 r + l16][16 c + q]
+                    const bool on = B.r(b) == B.c(b);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const bool diag = cb == w && l16 == q + 4 * r;
-                        sh.Dt[lo + (16 * cb + 4 * r) * (TS + 1)] =
-                            make_double2(diag ? xr[cb][r] + ivj : xr[cb][r], xi[cb][r]);
+                        const bool diag = on && l16 == q + 4 * r;
+                        sh.Dt[lo + 4 * r * (TS + 1)] = make_double2(diag ? xr[b][r] + iv[b] : xr[b][r], xi[b][r]);
                     }
                 }
                 __syncthreads();
