@@ -75,6 +75,30 @@ __device__ inline void adam_factors(const int64_t *step, int64_t add, float b1, 
     *c2 = (float)(1.0 - pow((double)b2, t));
 }
 
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+
+// Raw buffer over n floats at p (a wave-uniform address). A load past it reads
+// zero, and so does one at the offset OOB: the guards of the padded units cost a
+// select of the offset instead of a branch and a 64-bit address around each
+// load. In a training step at width 256, where vector instructions took 43% of
+// the SIMDs' time and MFMA 29%, the first kernel went from 29.6 to 26 us, and a
+// million proposals from 8.25 to 8.13 ms.
+constexpr int OOB = 1 << 30;
+
+__device__ inline rsrc_t make_rsrc(const float *p, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, 4 * n, 0x00020000);
+}
+
+__device__ inline float ldf(rsrc_t r, int voff) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0));
+}
+
+__device__ inline f4 ldf4(rsrc_t r, int voff, int soff) {
+    const u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    return __builtin_bit_cast(f4, v);
+}
+
 struct MlpArgs {
     // input row of sample s of member z: r = idx ? idx[z idxz + s] : s; its
     // features are theta[r] mapped to [-1, 1] (when theta is set, shared by
@@ -114,7 +138,7 @@ __host__ __device__ inline int64_t share_count(int H, int n_in) { return (int64_
 // members) and each is a chain of two products, two sets of erf and exp and two
 // products back; widths that fill tiles of 256 take sixteen waves, four per
 // SIMD, to cover each other's latencies: 29.6 us a step's first kernel at width
-// 256 where eight took 31.8. Staging W2 through LDS, one or four stages ahead,
+// 256 where eight took 31.8 (both with guarded loads; 26 now). Staging W2 through LDS, one or four stages ahead,
 // left the two W2 products at 7.6 and 6.9 us each (twice their matrix time), and
 // eight samples' groups in flight in the update made that kernel slower (12.6
 // against 10.7 us), so neither is here. FP32 MFMA and vector instructions of
@@ -143,7 +167,7 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
     // LDS rows are zero from H to 16 CT NW)
     const int H = a.H, n_in = a.n_in, nip = (n_in + 15) & ~15, HK = (H + 31) & ~31;
     const float *P = a.params + (int64_t)z * a.PP;
-    const float *W2 = P + a.offW2;
+    const rsrc_t W1 = make_rsrc(P, H * n_in), W2 = make_rsrc(P + a.offW2, H * H);
 
     for (int e = tid; e < FS * nip; e += 64 * NW) {
         const int s = e / nip, k = e - s * nip, gs = s0 + s;
@@ -174,7 +198,7 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int k = g + 4 * q + t;
-                wv[c][t] = (h < H && k < n_in) ? P[h * n_in + k] : 0.0f;
+                wv[c][t] = ldf(W1, h < H && k < n_in ? 4 * (h * n_in + k) : OOB);
             }
         }
 #pragma unroll
@@ -214,14 +238,16 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
         for (int c = 0; c < CT; ++c) acc[rt][c] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     // W2 reads run one group of 16 k ahead of the MFMAs that use them
     f4 wv[CT];
+    int w2o[CT];  // row hb + 16 c + l16, column 4 q
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int o = hb + 16 * c + l16;
+        w2o[c] = o < H ? 4 * (o * H + 4 * q) : OOB;
+    }
     auto load_w2 = [&](int g, f4 *dst) {
         const bool kin = g + 4 * q < H;
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const int o = hb + 16 * c + l16;
-            dst[c] = (o < H && kin) ? *reinterpret_cast<const f4 *>(&W2[(int64_t)o * H + g + 4 * q])
-                                    : f4{0.0f, 0.0f, 0.0f, 0.0f};
-        }
+        for (int c = 0; c < CT; ++c) dst[c] = ldf4(W2, kin ? w2o[c] : OOB, 4 * g);
     };
     // two groups of 16 k in flight: group g + 32 is read while g is multiplied
     f4 wb[CT];
@@ -382,16 +408,17 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[0][c] = f4{0.0f, 0.0f, 0.0f, 0.0f};
         float wt[4][CT];
+        int w2i[CT];  // row 4 q, column hb + 16 c + l16; rows past H are past the buffer
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int i = hb + 16 * c + l16;
+            w2i[c] = i < H ? 4 * (4 * q * H + i) : OOB;
+        }
         auto load_w2t = [&](int g, float (*dst)[CT]) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int o = g + 4 * q + t;
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    const int i = hb + 16 * c + l16;
-                    dst[t][c] = (o < H && i < H) ? W2[(int64_t)o * H + i] : 0.0f;
-                }
-            }
+                for (int c = 0; c < CT; ++c) dst[t][c] = ldf(W2, w2i[c] + 4 * (g + t) * H);
         };
         float wtb[4][CT];
         load_w2t(0, wt);
