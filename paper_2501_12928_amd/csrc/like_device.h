@@ -164,6 +164,90 @@ __device__ __forceinline__ void tile_update(rsrc_t A, rsrc_t P, rsrc_t Q, int K,
     }
 }
 
+// The 16 x 16 blocks of a diagonal tile that wave w forms: of the ten in the
+// lower triangle (the factorisation reads no others) three each, one the last
+// wave, in place of four each with six above the diagonal: 9 instead of 12
+// products a step. Block b lies in rows 16 r(b), columns 16 c(b): (x1, x0), (x1,
+// x1), (p2, q2); the last wave's second and third are not used. 512 theta at n =
+// 4096 599 -> 595 ms, 256 at n = 2048 39.5 -> 38.9 ms; where the update of a
+// diagonal tile is part of the chain, one theta at n = 4096 1.87 -> 1.72 ms.
+struct DiagBlocks {
+    int x0, x1, p2, q2;
+    __device__ DiagBlocks(int w) : x0(w == 3 ? 2 : 0), x1(w == 0 ? 1 : w == 1 ? 2 : 3), p2(w == 0 ? 0 : x1), q2(w == 0 ? 0 : 1) {}
+    __device__ int r(int b) const { return b < 2 ? x1 : p2; }
+    __device__ int c(int b) const { return b == 0 ? x0 : b == 1 ? x1 : q2; }
+};
+
+// Rows 16 x + l16 of one step of the panel, for the four slabs of DiagBlocks.
+struct DiagStep {
+    double2 x0, x1, p2, q2;
+};
+
+__device__ __forceinline__ void mma_diag(const DiagStep &s, d4 t1[3], d4 t2[3], d4 t3[3]) {
+    auto block = [&](int b, double2 p, double2 q) {
+        t1[b] = mfma64(q.x, p.x, t1[b]);
+        t2[b] = mfma64(q.y, p.y, t2[b]);
+        t3[b] = mfma64(q.x - q.y, p.x + p.y, t3[b]);
+    };
+    block(0, s.x1, s.x0);
+    block(1, s.x1, s.x1);
+    block(2, s.p2, s.q2);
+}
+
+// tile_update for a diagonal tile of side 64 (A its storage tile, Q the row panel),
+// in the blocks of DiagBlocks.
+template <int STAGES>
+__device__ __forceinline__ void diag_update(rsrc_t A, rsrc_t Q, int K, int voff, const DiagBlocks &B, d4 xr[3],
+                                            d4 xi[3]) {
+    constexpr int COLB = TS * 16;
+    auto load = [&](DiagStep &s, int soff) {
+        s.x0 = ld2(Q, voff, soff + 256 * B.x0);
+        s.x1 = ld2(Q, voff, soff + 256 * B.x1);
+        s.p2 = ld2(Q, voff, soff + 256 * B.p2);
+        s.q2 = ld2(Q, voff, soff + 256 * B.q2);
+    };
+    d4 t1[3], t3[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int so = (16 * B.c(b) + 4 * r) * A_COL_BYTES + 256 * B.r(b);
+            xr[b][r] = ld1(A, voff, so);
+            t3[b][r] = ld1(A, voff + 8, so);
+        }
+    }
+    DiagStep buf[STAGES];
+#pragma unroll
+    for (int s0 = 0; s0 < STAGES - 1; ++s0) {
+        load(buf[s0], 4 * s0 * COLB);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        t1[b] = d4{0, 0, 0, 0};
+        t3[b] = xr[b] - t3[b];
+        xr[b] = -xr[b];  // T2
+    }
+    d4 *t2 = xr;
+    for (int k0 = 0; k0 < K; k0 += 4 * STAGES) {
+        if ((k0 & (ALIGN_COLS - 1)) == 0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < STAGES; ++u) {
+            const int kl = min(k0 + 4 * (u + STAGES - 1), K - 4);
+            load(buf[(u + STAGES - 1) % STAGES], kl * COLB);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_diag(buf[u], t1, t2, t3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const d4 a = t1[b], c = t2[b];
+        xr[b] = -(a + c);
+        xi[b] = a - c - t3[b];
+    }
+}
+
 // Column boundary. Tiles of L and entries of w written in one column are read
 // in later columns by other waves of the workgroup. The workgroup-scope
 // release and acquire of __syncthreads make that safe only through the CU's

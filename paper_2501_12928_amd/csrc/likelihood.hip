@@ -101,6 +101,10 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
         }
     }
 
+    // A diagonal tile of side 64 is formed in its lower triangle only
+    constexpr bool lower = S == 64;
+    const DiagBlocks B(w);
+
     // Row 16 w + l16 of every diagonal tile, in the waves of group 0: the lane
     // with q = 0 sums |y|^2 over the columns, the one with q = 1 ln dg.
     double acc = 0.0;
@@ -119,13 +123,17 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
             // Operands of the diagonal phase, in flight during the tile update:
             // w_j, and the bin or inverse variance of this lane's row.
             double2 wj = make_double2(0.0, 0.0);
-            int32_t bj = 0;
-            double ivj = 0.0;
+            int32_t bj[2] = {0, 0};  // row of w, or (lower) rows of x1 and p2
+            double ivj[2] = {0.0, 0.0};
             if (u == 0) {
                 const int64_t g0 = (int64_t)j * S;
                 if (tid < S) wj = ldd2(yv + g0 + tid);
-                bj = ldg(I.coef_bin + g0 + 16 * w + l16);
-                ivj = ldg(I.coef_inv + g0 + 16 * w + l16);
+#pragma unroll
+                for (int e = 0; e < (lower ? 2 : 1); ++e) {
+                    const int64_t row = g0 + 16 * (!lower ? w : e == 0 ? B.x1 : B.p2) + l16;
+                    bj[e] = ldg(I.coef_bin + row);
+                    ivj[e] = ldg(I.coef_inv + row);
+                }
             }
             if (u < units) {
                 // ---- X = A_ij - sum_k L_ik L_jk^H, in the accumulator layout.
@@ -134,8 +142,13 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
                 constexpr int M = TS / S;
                 const int64_t aoff = tile_index(i / M, j / M) * TS2 + (int64_t)(S * (j % M)) * TS + S * (i % M) + 16 * w;
                 const rsrc_t Ar = make_rsrc(Ab + aoff, (int64_t)(tile_index(i / M, j / M) + 1) * TS2 * 16 - aoff * 16);
-                const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * S2 + 16 * w, (int64_t)K * COLB);
-                tile_update<S, STAGES>(Ar, Pr, Qr, K, voff, voffA, xr, xi);
+                if (lower && u == 0) {
+                    diag_update<STAGES>(make_rsrc(Ab + tile_index(j, j) * TS2, (int64_t)TS2 * 16), Qr, K, voff, B, xr,
+                                        xi);
+                } else {
+                    const rsrc_t Pr = make_rsrc(L + tile_index(i, 0) * S2 + 16 * w, (int64_t)K * COLB);
+                    tile_update<S, STAGES>(Ar, Pr, Qr, K, voff, voffA, xr, xi);
+                }
             } else {
                 panel_barriers(K);  // no tile for this group in the last round
                 // Defined on this path too: otherwise the compiler carries the
@@ -146,16 +159,19 @@ __device__ __forceinline__ void run_task(Shared &sh, double2 *L, double2 *yv, co
             if (u == 0) {
                 // D = X + diag(Phi^{-1}) -> LDS (column-major, leading dimension S + 1)
                 const int lane = opaque(threadIdx.x & 63), l16 = lane & 15, q = lane >> 4;
-                if (bj >= 0)
-                    ivj = bj < BIN_TABLE ? sh.invphi[bj] : 1.0 / (I.bin_scale[bj] * exp10(th[bj]));
-                const int lo = q * (S + 1) + 16 * w + l16;  // [16w + l16][q]
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
+                for (int e = 0; e < (lower ? 2 : 1); ++e)
+                    if (bj[e] >= 0) ivj[e] = bj[e] < BIN_TABLE ? sh.invphi[bj[e]] : 1.0 / (I.bin_scale[bj[e]] * exp10(th[bj[e]]));
+#pragma unroll
+                for (int cb = 0; cb < (lower ? 3 : NCB); ++cb) {
+                    if (lower && w == 3 && cb > 0) break;
+                    const int rb = lower ? B.r(cb) : w, cc = lower ? B.c(cb) : cb;
+                    const double iv = ivj[lower && cb == 2 ? 1 : 0];
+                    const int lo = (16 * cc + q) * (S + 1) + 16 * rb + l16;  // [16 rb + l16][16 cc + q]
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const bool diag = cb == w && l16 == q + 4 * r;
-                        sh.Dt[lo + (16 * cb + 4 * r) * (S + 1)] =
-                            make_double2(diag ? xr[cb][r] + ivj : xr[cb][r], xi[cb][r]);
+                        const bool diag = cc == rb && l16 == q + 4 * r;
+                        sh.Dt[lo + 4 * r * (S + 1)] = make_double2(diag ? xr[cb][r] + iv : xr[cb][r], xi[cb][r]);
                     }
                 }
                 if (tid < S) sh.wv[tid] = wj;

@@ -212,35 +212,6 @@ __device__ __forceinline__ bool spread_sum(SpreadShared &sh, const double2 *A, c
                           [&](int k, int e) { accumulate(Pr, Qr, k, e, voff, t1, xr, t3); });
 }
 
-// The 16 x 16 blocks of a diagonal tile that wave w forms: of the ten in the
-// lower triangle (the factorisation reads no others) three each, one the last
-// wave, in place of four each with six above the diagonal: the last update, which
-// is part of the chain, takes 9 instead of 12 products a step. Block b lies in
-// rows 16 r(b), columns 16 c(b): (x1, x0), (x1, x1), (p2, q2); the last wave's
-// second and third are not used.
-struct DiagBlocks {
-    int x0, x1, p2, q2;
-    __device__ DiagBlocks(int w) : x0(w == 3 ? 2 : 0), x1(w == 0 ? 1 : w == 1 ? 2 : 3), p2(w == 0 ? 0 : x1), q2(w == 0 ? 0 : 1) {}
-    __device__ int r(int b) const { return b < 2 ? x1 : p2; }
-    __device__ int c(int b) const { return b == 0 ? x0 : b == 1 ? x1 : q2; }
-};
-
-// Rows 16 x + l16 of one step of the panel, for the four slabs of DiagBlocks.
-struct DiagStep {
-    double2 x0, x1, p2, q2;
-};
-
-__device__ __forceinline__ void mma_diag(const DiagStep &s, d4 t1[3], d4 t2[3], d4 t3[3]) {
-    auto block = [&](int b, double2 p, double2 q) {
-        t1[b] = mfma64(q.x, p.x, t1[b]);
-        t2[b] = mfma64(q.y, p.y, t2[b]);
-        t3[b] = mfma64(q.x - q.y, p.x + p.y, t3[b]);
-    };
-    block(0, s.x1, s.x0);
-    block(1, s.x1, s.x1);
-    block(2, s.p2, s.q2);
-}
-
 // accumulate for a diagonal tile: P = Q, the blocks of DiagBlocks.
 __device__ __forceinline__ void accumulate_diag(rsrc_t Q, int k0, int k1, int voff, const DiagBlocks &B, d4 t1[3],
                                                 d4 t2[3], d4 t3[3]) {
