@@ -64,12 +64,11 @@ struct HerkStep {
     double wgt;
 };
 
-__device__ inline void herk_load(HerkStep &st, rsrc_t Trow, rsrc_t W, int vp, const int vq[4], int vw,
-                                 int soff_w) {
+__device__ inline void herk_load(HerkStep &st, rsrc_t Trow, rsrc_t Wrow, int vp, const int vq[4], int vw) {
     st.p = ld2(Trow, vp, 0);
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) st.qv[cb] = ld2(Trow, vq[cb], 0);
-    st.wgt = ld1(W, vw, soff_w);
+    st.wgt = ld1(Wrow, vw, 0);
 }
 
 // conj(p) q with p weighted, three real products (Gauss):
@@ -122,34 +121,31 @@ __global__ __launch_bounds__(256, 2) void herk_fp64_kernel(const double2 *__rest
         const int64_t col = TS * tj + 16 * cb + l16;
         vq[cb] = col < n ? (int)((q * ldT + col) * 16) : OOB;
     }
-    const rsrc_t W = make_rsrc(invvar, m * 8);
     const int vw = q * 8;
 
     d4 t1[4], t2[4], t3[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) t1[cb] = t2[cb] = t3[cb] = d4{0, 0, 0, 0};
 
-    // Block of rows s..s+3: descriptor based at row s, sized to the rows
-    // that exist. rows_per is a multiple of 64, so a step of this split never
+    // Block of rows s..s+3 of T and of the weights: descriptors based at row s,
+    // sized to the rows that exist. rows_per is a multiple of 64, so a step of this split never
     // holds rows of the next; past m the descriptor reads zeros, which add
     // nothing. The prefetch past r1 is never used.
-    auto rows_at = [&](int64_t s) {
-        const int64_t at = s < m ? s : m;
-        return make_rsrc(T + at * ldT, (m - at < 4 ? m - at : 4) * ldT * 16);
+    auto load = [&](HerkStep &st, int64_t s) {
+        const int64_t at = s < m ? s : m, rows = m - at < 4 ? m - at : 4;
+        herk_load(st, make_rsrc(T + at * ldT, rows * ldT * 16), make_rsrc(invvar + at, rows * 8), vp, vq, vw);
     };
     HerkStep buf[HERK_STAGES];
 #pragma unroll
     for (int s0 = 0; s0 < HERK_STAGES - 1; ++s0) {
-        const int64_t s = r0 + 4 * s0;
-        herk_load(buf[s0], rows_at(s), W, vp, vq, vw, (int)(s * 8));
+        load(buf[s0], r0 + 4 * s0);
         __builtin_amdgcn_sched_barrier(0);
     }
     for (int64_t s0 = r0; s0 < r1; s0 += 4 * HERK_STAGES) {
         if (((s0 - r0) & (TS - 1)) == 0) __syncthreads();
 #pragma unroll
         for (int u = 0; u < HERK_STAGES; ++u) {
-            const int64_t sl = s0 + 4 * (u + HERK_STAGES - 1);
-            herk_load(buf[(u + HERK_STAGES - 1) % HERK_STAGES], rows_at(sl), W, vp, vq, vw, (int)(sl * 8));
+            load(buf[(u + HERK_STAGES - 1) % HERK_STAGES], s0 + 4 * (u + HERK_STAGES - 1));
             __builtin_amdgcn_sched_barrier(0);
             herk_step(buf[u], t1, t2, t3);
             __builtin_amdgcn_sched_barrier(0);
