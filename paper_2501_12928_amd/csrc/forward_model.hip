@@ -132,8 +132,8 @@ __device__ __forceinline__ double2 phase(const Pix &x, bool in, double fc, doubl
 // phase factors, which are made once for all waves, pass through LDS, in stages
 // of 32 pixels with one barrier each. (With both staged through LDS, 16 pixels
 // and two barriers a stage, the waves of a workgroup held each other up: matrix
-// cores busy 69% of the time, 1.19 ms for 20000 x 4096. Now 84%, 1.11 ms; at the
-// clock it runs at, 2.1 GHz, the products alone take 0.94 ms. Two LDS buffers of
+// cores busy 71% of a counter run, 1.19 ms for 20000 x 4096. Now 77%, 1.11 ms; at
+// the clock it runs at, 2.1 GHz, the products alone take 0.94 ms. Two LDS buffers of
 // 8 pixels instead gave 1.18.) At most 256 registers per lane (two workgroups
 // per CU): the accumulators then live in ordinary vector registers, with no
 // copies to and from the accumulation registers.
