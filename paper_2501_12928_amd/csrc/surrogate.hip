@@ -55,8 +55,12 @@ __device__ inline f4 mfma32(float a, float b, f4 c) {
 
 __device__ inline float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
-__device__ inline float gelu_grad_f(float x) {
-    return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * expf(-0.5f * x * x) * 0.39894228040143268f;
+// GELU and its derivative from one erf (erf branches, so that two calls are not
+// merged by the compiler: a training step 36.5 -> 34.9 us).
+__device__ inline float gelu_and_grad(float x, float *grad) {
+    const float c = 1.0f + erff(x * 0.70710678118654752f);
+    *grad = 0.5f * c + x * expf(-0.5f * x * x) * 0.39894228040143268f;
+    return 0.5f * x * c;
 }
 
 // Adam with bias-corrected moments, c1 = 1 - beta1^t, c2 = 1 - beta2^t.
@@ -222,8 +226,13 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float zz = acc[rt][c][r] + b;
-                hv[r] = gelu_f(zz);
-                if constexpr (BWD) g1[c][r] = gelu_grad_f(zz);
+                if constexpr (BWD) {
+                    float grad;
+                    hv[r] = gelu_and_grad(zz, &grad);
+                    g1[c][r] = grad;
+                } else {
+                    hv[r] = gelu_f(zz);
+                }
                 hs[(ST * rt + 4 * q + r) * HS + h] = hv[r];
             }
             if constexpr (BWD) *reinterpret_cast<f4 *>(&a.H1T[((int64_t)z * HP + h) * a.nbp + s0 + 4 * q]) = hv;
@@ -288,8 +297,9 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float zz = acc[0][c][r] + b;
-                h2[c][r] = gelu_f(zz);
-                gw[c][r] = w3v[c] * gelu_grad_f(zz);
+                float grad;
+                h2[c][r] = gelu_and_grad(zz, &grad);
+                gw[c][r] = w3v[c] * grad;
             }
         }
         if ((w & 1) == 0) {
@@ -323,11 +333,15 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float zz = acc[rt][c][r] + b;
-                    const float hv = gelu_f(zz);
+                    float hv, grad;
+                    if constexpr (BWD)
+                        hv = gelu_and_grad(zz, &grad);
+                    else
+                        hv = gelu_f(zz);
                     fp[rt][r] += hv * w3;
                     if constexpr (BWD) {
                         h2[c][r] = hv;
-                        gw[c][r] = w3 * gelu_grad_f(zz);
+                        gw[c][r] = w3 * grad;
                     }
                 }
         }
