@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "vectors.h"
 
 namespace eor {
 
@@ -210,10 +211,9 @@ __global__ __launch_bounds__(256) void vectors_kernel(const double2 *__restrict_
                                                       const double2 *__restrict__ d, int64_t rows_per,
                                                       double *__restrict__ invvar, double2 *__restrict__ partial,
                                                       double2 *__restrict__ scal_part) {
-    __shared__ double2 red[4][64];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t j = (int64_t)blockIdx.x * 64 + lane, split = blockIdx.y;
-    const int64_t s_lo = split * rows_per, s_hi = s_lo + rows_per < m ? s_lo + rows_per : m;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t s_lo = (int64_t)blockIdx.y * rows_per, s_hi = s_lo + rows_per < m ? s_lo + rows_per : m;
     double sr = 0.0, si = 0.0;
     if (j < n) {
         int64_t s = s_lo + w;
@@ -236,39 +236,7 @@ __global__ __launch_bounds__(256) void vectors_kernel(const double2 *__restrict_
             si += (t.x * ds.y - t.y * ds.x) * wv;
         }
     }
-    red[w][lane] = make_double2(sr, si);
-    __syncthreads();
-    if (w == 0 && j < n) {
-        double2 v = red[0][lane];
-#pragma unroll
-        for (int u = 1; u < 4; ++u) {
-            v.x += red[u][lane].x;
-            v.y += red[u][lane].y;
-        }
-        partial[split * n + j] = v;
-    }
-    if (blockIdx.x != 0) return;
-    double c = 0.0, l = 0.0;
-    for (int64_t s = s_lo + tid; s < s_hi; s += 256) {
-        const double nv = noise_var[s];
-        const double2 ds = d[s];
-        invvar[s] = 1.0 / nv;
-        c += (ds.x * ds.x + ds.y * ds.y) / nv;
-        l += log(nv);
-    }
-    // fixed tree, so that the result does not depend on timing
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        c += __shfl_xor(c, o);
-        l += __shfl_xor(l, o);
-    }
-    __syncthreads();
-    if (lane == 0) red[w][0] = make_double2(c, l);
-    __syncthreads();
-    if (tid == 0) {
-        const double2 a = red[0][0], b = red[1][0], e = red[2][0], f = red[3][0];
-        scal_part[split] = make_double2((a.x + b.x) + (e.x + f.x), (a.y + b.y) + (e.y + f.y));
-    }
+    vectors_finish(make_double2(sr, si), s_lo, s_hi, j, n, noise_var, d, invvar, partial, scal_part);
 }
 
 // The slices' sums, in order: dbar (zero in the padding), and by one more
@@ -395,6 +363,11 @@ hipError_t launch_precompute_vectors(const Context &c, const double2 *T, int64_t
     double2 *scal_part = partial + (int64_t)splits * c.n;
     hipLaunchKernelGGL(vectors_kernel, dim3((unsigned)((c.n + 63) / 64), (unsigned)splits), dim3(256), 0, s, T, ldT,
                        c.m, c.n, noise_var, d, rows, invvar, partial, scal_part);
+    return launch_vectors_reduce(c, partial, scal_part, splits, s);
+}
+
+hipError_t launch_vectors_reduce(const Context &c, const double2 *partial, const double2 *scal_part, int splits,
+                                 hipStream_t s) {
     hipLaunchKernelGGL(vectors_reduce_kernel, dim3((unsigned)(c.n_pad / 16 + 1)), dim3(64), 0, s, partial, scal_part,
                        splits, c.n, c.n_pad, c.dbar, c.scal);
     return hipGetLastError();
