@@ -316,9 +316,8 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
     EOR_TRY(hipMemcpyAsync(c.d_inst, c.h_inst, c.tab_bytes, hipMemcpyHostToDevice, s), "copy tables");
 
     const double2 *Td = (const double2 *)T;
-    // the split into bfloat16 terms forms the vectors in its own pass over T
-    const bool bf16 = prec == EOR_PREC_BF16X3 || prec == EOR_PREC_BF16X2;
-    if (!bf16)
+    // the reduced precisions form the vectors in their own pass over T
+    if (prec == EOR_PREC_FP64)
         EOR_TRY(eor::launch_precompute_vectors(c, Td, ldT, noise_var, (const double2 *)d, c.invvar, c.partial,
                                                c.splits, s),
                 "precompute vectors");
@@ -337,10 +336,11 @@ eor_status eor_precompute(eor_ctx *ctx, int64_t m, int64_t n, const void *T, int
     if (prec == EOR_PREC_FP64)
         EOR_TRY(eor::launch_precompute_fp64(c, Td, ldT, c.invvar, c.lowp, s), "precompute A (fp64)");
     else if (prec == EOR_PREC_FP32)
-        EOR_TRY(eor::launch_precompute_fp32(c, Td, ldT, c.invvar, c.lowp, s), "precompute A (fp32)");
+        EOR_TRY(eor::launch_precompute_fp32(c, Td, ldT, noise_var, (const double2 *)d, c.lowp, s),
+                "precompute A (fp32)");
     else
-        EOR_TRY(eor::launch_precompute_bf16(c, Td, ldT, noise_var, (const double2 *)d, c.invvar, c.partial, c.splits,
-                                            c.lowp, prec == EOR_PREC_BF16X3 ? 3 : 2, s),
+        EOR_TRY(eor::launch_precompute_bf16(c, Td, ldT, noise_var, (const double2 *)d, c.lowp,
+                                            prec == EOR_PREC_BF16X3 ? 3 : 2, s),
                 "precompute A (bf16)");
 #undef EOR_TRY
     e = c.order.leave(s);

@@ -187,11 +187,10 @@ hipError_t launch_herk_reduce(const double2 *part, int64_t tiles, int splits, in
 hipError_t launch_precompute_fp64(const Context &c, const double2 *T, int64_t ldT,
                                   const double *invvar, void *scratch, hipStream_t s);
 size_t lowp_scratch_bytes(eor_precision prec, int64_t m, int64_t n_pad, int num_cu);
-hipError_t launch_precompute_fp32(const Context &c, const double2 *T, int64_t ldT,
-                                  const double *invvar, void *scratch, hipStream_t s);
+hipError_t launch_precompute_fp32(const Context &c, const double2 *T, int64_t ldT, const double *noise_var,
+                                  const double2 *d, void *scratch, hipStream_t s);
 hipError_t launch_precompute_bf16(const Context &c, const double2 *T, int64_t ldT, const double *noise_var,
-                                  const double2 *d, double *invvar, double2 *partial, int vec_splits, void *scratch,
-                                  int nterm, hipStream_t s);
+                                  const double2 *d, void *scratch, int nterm, hipStream_t s);
 hipError_t launch_vectors_reduce(const Context &c, const double2 *partial, const double2 *scal_part, int splits,
                                  hipStream_t s);
 int vectors_splits(int64_t m, int64_t n, int num_cu);
