@@ -403,7 +403,7 @@ static eor_status loglike_impl(eor_ctx *ctx, int64_t B, const double *theta, dou
         p.ntask = (int32_t)nb;
         p.n_max = (int32_t)c.N;
         p.units = nb * eor::n_tiles(c.N);
-        p.per_cu = eor::spread_per_cu(eor::spread_chain_us(c.N), nb * eor::spread_work_us(c.N));
+        p.per_cu = eor::spread_per_cu(eor::spread_chain_us(c.N), nb * eor::spread_work_us(c.N), c.N);
         p.counter = c.counter;
         p.prog = c.prog;
         p.Lw = c.Lw;

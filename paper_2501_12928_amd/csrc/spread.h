@@ -51,10 +51,14 @@ inline double spread_us(double chain, double work) {
 
 // Where the chain bounds, one workgroup per CU: a second one's matrix
 // instructions hold up the single wave that factors a diagonal tile (19 us
-// beside them, 14 alone). One against two per CU: n = 4096, one theta 1.93
-// against 2.30 ms, two 2.83 / 2.98, four 5.06 / 4.99; n = 2048, four 1.04 / 1.19,
-// 16 3.04 / 2.82; n = 1003, eight 498 / 570 us, 16 633 / 684, 24 881 / 793; n =
-// 200, 128 theta (the work 1.17 times the chain) 241 / 226.
-inline int spread_per_cu(double chain, double work) { return work < 1.1 * chain ? 1 : 2; }
+// beside them, 14 alone). With much more work than chain, two, so that one
+// computes while the other waits. The line, as work over chain, rises with the
+// tile rows N, since longer sums leave less waiting to cover. Measured, one
+// against two per CU: N = 4, 64 theta (work 0.6 times the chain) 164 / 162 us; N = 9,
+// 32 (0.9) 364 / 378, 40 (1.1) 415 / 388; N = 16, 14 (1.0) 550 / 638, 24 (1.6) 859 /
+// 744; N = 24, 10 (1.3) 932 / 1022, 12 (1.6) 1129 / 1092; N = 32, 8 (1.8) 1531 /
+// 1563, 10 (2.2) 1955 / 1830; N = 47, 4 (1.8) 2.21 / 2.37 ms, 6 (2.6) 3.19 / 3.18; N =
+// 64, two (1.6) 2.64 / 3.06, four (3.1) 4.94 / 5.12.
+inline int spread_per_cu(double chain, double work, int64_t N) { return work < (0.5 + N / 22.0) * chain ? 1 : 2; }
 
 }  // namespace eor
