@@ -162,7 +162,7 @@ int64_t spread_count(const Context &c, int64_t B, int64_t round) {
     if (c.tune.ts != eor::TS) return 0;
     auto better = [&](int64_t n) {
         const double lone = eor::lone_us(c.N) * (1.0 + 0.15 * std::min<double>(1.0, (double)n / c.num_cu));
-        return n > 0 && eor::spread_us(eor::spread_chain_us(c.N), n * eor::spread_work_us(c.N)) < 0.97 * lone &&
+        return n > 0 && eor::spread_us(eor::spread_chain_us(c.N), n * eor::spread_work_us(c.N), c.N) < 0.97 * lone &&
                n * eor::n_tiles(c.N) < ((int64_t)1 << 31) - 4096;
     };
     if (B >= round && better(round)) return B;

@@ -158,7 +158,7 @@ hipError_t build_spread(eor_group &g, const std::vector<int2> &tasks) {
         ++count[N];
     }
     for (int64_t r = N_max; r > 0; --r) count[r - 1] += count[r];
-    g.est_spread = eor::spread_us(chain, work);
+    g.est_spread = eor::spread_us(chain, work, N_max);
     g.spread_per_cu = eor::spread_per_cu(chain, work, N_max);
     g.spread_rows = N_max;
     g.spread_elems = elems;

@@ -41,11 +41,15 @@ hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s);
 //  - spread, a theta's diagonal tiles follow one another every 27 us, and its
 //    N (N + 1) / 2 tiles take the whole GPU 0.08 us each plus their products at
 //    78 TFLOP/s. The chain and the work of all theta overlap almost wholly where
-//    the chain is the longer, in part otherwise.
+//    the chain is the longer, in part otherwise; with two to four tile rows there
+//    is too little of either, and they add up (spread against one workgroup each:
+//    n = 128, 60 theta 78 / 81 us, 128 109 / 89; n = 200, 64 160 / 205, 128 214 /
+//    205, where the sum without this said spread in all four).
 inline double lone_us(int64_t N) { return 30.0 * N + 1.5 * N * N + 0.93 * N * N * N; }
 inline double spread_chain_us(int64_t N) { return 27.0 * N; }
 inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 * 262144.0 * N * N * N / 78e6; }
-inline double spread_us(double chain, double work) {
+inline double spread_us(double chain, double work, int64_t N) {
+    if (N >= 2 && N <= 4) return chain + work;
     return chain > work ? chain + 0.1 * work : work + 0.3 * chain;
 }
 
