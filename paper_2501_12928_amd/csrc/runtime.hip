@@ -32,6 +32,8 @@ struct eor_group {
     int64_t ntask = 0;
     // for theta spread over all workgroups: where each task's slot of L starts, the
     // tasks with at least r tile rows, the tiles in all, and the two estimates
+    std::vector<int64_t> spread_off;
+    std::vector<int32_t> spread_count;
     double2 *spread_y = nullptr;         // w and y of every task; the other arrays follow in the same allocation
     int64_t *d_off = nullptr;
     int32_t *d_count = nullptr;
@@ -131,17 +133,19 @@ void free_tasks(eor_group &g) {
     g.task_B.clear();
 }
 
-// What spreading every theta of the task list over all workgroups needs, if
-// the estimates say that it is sooner done: few theta, or few large ones that
-// would keep one workgroup each busy long after the others are done.
-hipError_t build_spread(eor_group &g, const std::vector<int2> &tasks) {
+// Whether spreading every theta of the task list over all workgroups is sooner
+// done by the estimates (few theta, or few large ones that would keep one
+// workgroup each busy long after the others are done), and what it needs.
+void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
     const int64_t n = (int64_t)tasks.size(), N_max = g.inst[tasks[0].x]->c.N;
     double chain = 0.0, work = 0.0;
     const double load = 1.0 + 0.15 * std::min(1.0, (double)n / g.num_cu);
     std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
     for (int i = 0; i < g.num_cu; ++i) busy.push(0.0);
-    std::vector<int64_t> off(n);
-    std::vector<int32_t> count(N_max + 1, 0);
+    std::vector<int64_t> &off = g.spread_off;
+    std::vector<int32_t> &count = g.spread_count;
+    off.assign(n, 0);
+    count.assign(N_max + 1, 0);
     int64_t elems = 0, units = 0;
     g.est_lone = 0.0;
     for (int64_t t = 0; t < n; ++t) {
@@ -163,22 +167,33 @@ hipError_t build_spread(eor_group &g, const std::vector<int2> &tasks) {
     g.spread_rows = N_max;
     g.spread_elems = elems;
     g.spread_units = units;
-    if (!(g.est_spread < 0.97 * g.est_lone) || units >= ((int64_t)1 << 31) - 4096) {
-        g.est_spread = INFINITY;
-        return hipSuccess;
-    }
-    const size_t y = (size_t)n * N_max * eor::TS, prog = (size_t)n * (N_max + eor::SPREAD_EXTRA);
-    const size_t bytes = y * sizeof(double2) + n * sizeof(int64_t) + (count.size() + prog) * sizeof(int32_t);
+    if (!(g.est_spread < 0.97 * g.est_lone) || units >= ((int64_t)1 << 31) - 4096) g.est_spread = INFINITY;
+}
+
+// The memory of a planned spread launch: false if it cannot be had. The launch
+// with one workgroup per theta needs none of it and is then taken.
+bool ensure_spread(eor_group &g) {
+    if (g.spread_y) return true;
+    const size_t n = (size_t)g.ntask, count = g.spread_count.size();
+    const size_t y = n * g.spread_rows * eor::TS, prog = n * (g.spread_rows + eor::SPREAD_EXTRA);
+    const size_t bytes = y * sizeof(double2) + n * sizeof(int64_t) + (count + prog) * sizeof(int32_t);
     hipError_t e = hipMalloc(&g.spread_y, bytes);
-    if (e != hipSuccess) return e;
-    g.d_off = (int64_t *)(g.spread_y + y);
-    g.d_count = (int32_t *)(g.d_off + n);
-    g.prog = g.d_count + count.size();
-    e = hipMemcpy(g.d_off, off.data(), n * sizeof(int64_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(g.d_count, count.data(), count.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        g.d_off = (int64_t *)(g.spread_y + y);
+        g.d_count = (int32_t *)(g.d_off + n);
+        g.prog = g.d_count + count;
+        e = hipMemcpy(g.d_off, g.spread_off.data(), n * sizeof(int64_t), hipMemcpyHostToDevice);
+    }
+    if (e == hipSuccess)
+        e = hipMemcpy(g.d_count, g.spread_count.data(), count * sizeof(int32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(g.prog, 0, prog * sizeof(int32_t));
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    return e;
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    if (g.spread_y) (void)hipFree(g.spread_y);
+    g.spread_y = nullptr;
+    g.est_spread = INFINITY;  // until the task list changes
+    return false;
 }
 
 // Task list: every theta of every instance, longest first (cost ~ N^3), so
@@ -210,11 +225,11 @@ eor_status build_tasks(eor_group &g, const int64_t *B) {
     if (tasks.empty()) return EOR_OK;
     hipError_t e = hipMalloc(&g.d_task, tasks.size() * sizeof(int2));
     if (e == hipSuccess) e = hipMemcpy(g.d_task, tasks.data(), tasks.size() * sizeof(int2), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = build_spread(g, tasks);
     if (e != hipSuccess) {
         free_tasks(g);
         return eor::hip_status(e, "task list");
     }
+    plan_spread(g, tasks);
     return EOR_OK;
 }
 
@@ -362,13 +377,14 @@ eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta,
     st = ensure_work(g, want);
     if (st != EOR_OK) return st;
     const int64_t grid = std::min<int64_t>(want, g.slots);
-    // Every theta spread over all workgroups, where that is sooner done and the
-    // workspace of the resident workgroups holds every theta's L (the tiles are
-    // then 64-wide: 32-wide ones sum in another order).
+    // Every theta spread over all workgroups, where that is sooner done, the
+    // workspace of the resident workgroups holds every theta's L and the tiles
+    // are 64-wide (32-wide ones sum in another order).
     bool spread = allow_spread && std::isfinite(g.est_spread) &&
                   g.spread_elems <= g.slots * g.slot_tiles * eor::TS2;
     for (size_t i = 0; i < g.inst.size(); ++i)
         spread = spread && (B[i] == 0 || g.h_inst[i].ts == eor::TS);
+    spread = spread && ensure_spread(g);
     const eor::LikeParams p = make_params(g, theta, logL, info);
     const eor::SpreadParams sp = spread ? make_spread(g, theta, logL, info) : eor::SpreadParams();
     auto launch = [&](hipStream_t st) {

@@ -1,0 +1,41 @@
+"""What a group call allocates for theta spread over all workgroups: nothing for
+launches that cannot be spread, and no call is refused for it."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import have_gpu
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="no GPU")]
+
+
+def _context(seed, n):
+    import torch
+    import paper_2501_12928_amd as eor
+    inst = synth.small(seed=seed, m=n + 40, n=n, n_k=1, n_theta=1)
+    return eor.Context(0).precompute(torch.from_numpy(inst.T).cuda(), torch.from_numpy(inst.noise_var).cuda(),
+                                     torch.from_numpy(inst.d).cuda(), 1, inst.bin_of, inst.fixed_var)
+
+
+def test_no_call_refused_for_the_spread_route():
+    """Five million small theta beside one at n = 4096. The estimates prefer the
+    spread route, whose arrays for all of them (64 KiB of solve vectors each at
+    the largest instance's size: 328 GB) no device holds; the route with one
+    workgroup per theta needs a slot per resident workgroup."""
+    import torch
+    import paper_2501_12928_amd as eor
+    B = 5_000_000
+    ctxs = [_context(1, 4096), _context(2, 40)]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    th = [-1.0 + 4.0 * torch.rand(b, 1, dtype=torch.float64, device="cuda", generator=g) for b in (1, B)]
+    grp = eor.Group(ctxs)
+    print(f"gpu: group of 1 + {B} theta", flush=True)
+    outs, infos = grp.loglike(th)
+    torch.cuda.synchronize()
+    assert all(bool((i == 0).all()) for i in infos)
+    for c, t, o in zip(ctxs, th, outs):
+        print(f"gpu: {t.shape[0]} theta of one context", flush=True)
+        assert torch.equal(c.loglike_batch(t)[0], o)
+    grp.close()
+    for c in ctxs:
+        c.close()
