@@ -22,6 +22,36 @@
 
 using eor::Context;
 
+namespace eor {
+
+// A device buffer that is kept while it is large enough.
+template <class T>
+struct DeviceArray {
+    T *p = nullptr;
+    size_t cap = 0;
+    // Room for n elements; true if the buffer is a new one.
+    hipError_t ensure(size_t n, bool *fresh = nullptr) {
+        if (fresh) *fresh = false;
+        if (n <= cap) return hipSuccess;
+        release();
+        const hipError_t e = hipMalloc(&p, n * sizeof(T));
+        if (e != hipSuccess) {
+            p = nullptr;
+            return e;
+        }
+        cap = n;
+        if (fresh) *fresh = true;
+        return hipSuccess;
+    }
+    void release() {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+        cap = 0;
+    }
+};
+
+}  // namespace eor
+
 struct eor_group {
     int device = 0;
     int num_cu = 0;
@@ -30,18 +60,20 @@ struct eor_group {
     eor::InstDesc *h_inst = nullptr;     // pinned staging
     int2 *d_task = nullptr;
     int64_t ntask = 0;
-    // for theta spread over all workgroups: where each task's slot of L starts, the
-    // tasks with at least r tile rows, the tiles in all, and the two estimates
-    std::vector<int64_t> spread_off;
-    std::vector<int32_t> spread_count;
-    double2 *spread_y = nullptr;         // w and y of every task; the other arrays follow in the same allocation
-    int64_t *d_off = nullptr;
-    int32_t *d_count = nullptr;
-    int32_t *prog = nullptr;             // progress words, zero between launches
-    int64_t spread_rows = 0, spread_elems = 0, spread_units = 0;
+    // For theta spread over all workgroups, of the task list: the two estimates,
+    // the tile rows of the largest instance, the elements of L and of y and the
+    // tiles in all. On the device, each kept while it is large enough: per task
+    // where its L and its y start, with the number of tasks of at least r tile
+    // rows behind them; w and y; the progress words (zero between launches).
+    eor::DeviceArray<int64_t> spread_tab;
+    eor::DeviceArray<double2> spread_y;
+    eor::DeviceArray<int32_t> prog;
+    bool spread_ready = false;           // spread_tab is that of the task list
+    int64_t spread_rows = 0, spread_elems = 0, spread_y_elems = 0, spread_units = 0;
     double est_spread = 0.0, est_lone = 0.0;
     int spread_per_cu = 2;
     std::vector<int64_t> task_B, task_N; // B and tile rows per instance the task list was built for
+    std::vector<int> order_N;            // the instances in list order, largest first
     unsigned int *counter = nullptr;
     double2 *Lw = nullptr;
     double2 *yw = nullptr;
@@ -127,9 +159,8 @@ eor_status ensure_work(eor_group &g, int64_t want) {
 
 void free_tasks(eor_group &g) {
     if (g.d_task) (void)hipFree(g.d_task);
-    if (g.spread_y) (void)hipFree(g.spread_y);
     g.d_task = nullptr;
-    g.spread_y = nullptr;
+    g.spread_ready = false;
     g.task_B.clear();
 }
 
@@ -142,11 +173,7 @@ void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
     const double load = 1.0 + 0.15 * std::min(1.0, (double)n / g.num_cu);
     std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
     for (int i = 0; i < g.num_cu; ++i) busy.push(0.0);
-    std::vector<int64_t> &off = g.spread_off;
-    std::vector<int32_t> &count = g.spread_count;
-    off.assign(n, 0);
-    count.assign(N_max + 1, 0);
-    int64_t elems = 0, units = 0;
+    int64_t elems = 0, y_elems = 0, units = 0;
     g.est_lone = 0.0;
     for (int64_t t = 0; t < n; ++t) {
         const int64_t N = g.inst[tasks[t].x]->c.N;
@@ -156,42 +183,55 @@ void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
         busy.pop();
         busy.push(end);
         g.est_lone = std::max(g.est_lone, end);
-        off[t] = elems;
         elems += eor::n_tiles(N) * eor::TS2;
+        y_elems += N * eor::TS;
         units += eor::n_tiles(N);
-        ++count[N];
     }
-    for (int64_t r = N_max; r > 0; --r) count[r - 1] += count[r];
     g.est_spread = eor::spread_us(chain, work, N_max);
     g.spread_per_cu = eor::spread_per_cu(chain, work, N_max);
     g.spread_rows = N_max;
     g.spread_elems = elems;
+    g.spread_y_elems = y_elems;
     g.spread_units = units;
     if (!(g.est_spread < 0.97 * g.est_lone) || units >= ((int64_t)1 << 31) - 4096) g.est_spread = INFINITY;
 }
 
 // The memory of a planned spread launch: false if it cannot be had. The launch
-// with one workgroup per theta needs none of it and is then taken.
+// with one workgroup per theta needs none of it and is then taken. (No earlier
+// spread launch is pending: a new task list has waited for the queued work.)
 bool ensure_spread(eor_group &g) {
-    if (g.spread_y) return true;
-    const size_t n = (size_t)g.ntask, count = g.spread_count.size();
-    const size_t y = n * g.spread_rows * eor::TS, prog = n * (g.spread_rows + eor::SPREAD_EXTRA);
-    const size_t bytes = y * sizeof(double2) + n * sizeof(int64_t) + (count + prog) * sizeof(int32_t);
-    hipError_t e = hipMalloc(&g.spread_y, bytes);
-    if (e == hipSuccess) {
-        g.d_off = (int64_t *)(g.spread_y + y);
-        g.d_count = (int32_t *)(g.d_off + n);
-        g.prog = g.d_count + count;
-        e = hipMemcpy(g.d_off, g.spread_off.data(), n * sizeof(int64_t), hipMemcpyHostToDevice);
+    if (g.spread_ready) return true;
+    const int64_t n = g.ntask;
+    const size_t words = (size_t)n * (g.spread_rows + eor::SPREAD_EXTRA);
+    bool fresh = false;
+    hipError_t e = g.spread_y.ensure(g.spread_y_elems);
+    if (e == hipSuccess) e = g.prog.ensure(words, &fresh);
+    if (e == hipSuccess && fresh) e = hipMemset(g.prog.p, 0, words * sizeof(int32_t));
+    if (e == hipSuccess && fresh) e = hipStreamSynchronize(nullptr);
+    // per task in list order (largest first) the starts of L and y, then the counts
+    std::vector<int64_t> tab(2 * n + g.spread_rows / 2 + 1);
+    int32_t *count = (int32_t *)(tab.data() + 2 * n);
+    int64_t t = 0, at = 0, y = 0;
+    for (int i : g.order_N) {
+        const int64_t N = g.task_N[i];
+        for (int64_t b = 0; b < g.task_B[i]; ++b, ++t) {
+            tab[2 * t] = at;
+            tab[2 * t + 1] = y;
+            at += eor::n_tiles(N) * eor::TS2;
+            y += N * eor::TS;
+        }
+        if (g.task_B[i] > 0)
+            for (int64_t r = 0; r <= N; ++r) count[r] += (int32_t)g.task_B[i];
     }
-    if (e == hipSuccess)
-        e = hipMemcpy(g.d_count, g.spread_count.data(), count * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(g.prog, 0, prog * sizeof(int32_t));
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e == hipSuccess) return true;
+    if (e == hipSuccess) e = g.spread_tab.ensure(tab.size());
+    if (e == hipSuccess) e = hipMemcpy(g.spread_tab.p, tab.data(), tab.size() * sizeof(int64_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        g.spread_ready = true;
+        return true;
+    }
     (void)hipGetLastError();
-    if (g.spread_y) (void)hipFree(g.spread_y);
-    g.spread_y = nullptr;
+    g.spread_y.release();
+    g.prog.release();         // its words may not have been cleared
     g.est_spread = INFINITY;  // until the task list changes
     return false;
 }
@@ -221,6 +261,7 @@ eor_status build_tasks(eor_group &g, const int64_t *B) {
     g.ntask = (int64_t)tasks.size();
     g.task_B = want;
     g.task_N = rows;
+    g.order_N = order;
     drop_graph(g);
     if (tasks.empty()) return EOR_OK;
     hipError_t e = hipMalloc(&g.d_task, tasks.size() * sizeof(int2));
@@ -323,17 +364,16 @@ eor::SpreadParams make_spread(const eor_group &g, const double *const *theta, do
     std::memset(&p, 0, sizeof(p));
     p.inst = g.d_inst;
     p.task = g.d_task;
-    p.count = g.d_count;
+    p.off = (const longlong2 *)g.spread_tab.p;
+    p.count = (const int32_t *)(g.spread_tab.p + 2 * g.ntask);
     p.ntask = (int32_t)g.ntask;
     p.n_max = (int32_t)g.spread_rows;
     p.units = g.spread_units;
     p.per_cu = g.spread_per_cu;
     p.counter = g.counter;
-    p.prog = g.prog;
+    p.prog = g.prog.p;
     p.Lw = g.Lw;
-    p.off = g.d_off;
-    p.yw = g.spread_y;
-    p.slot_y = g.spread_rows * eor::TS;
+    p.yw = g.spread_y.p;
     for (size_t i = 0; i < g.inst.size(); ++i)
         p.call[i] = eor::CallDesc{theta[i], logL[i], info ? info[i] : nullptr, nullptr};
     return p;
@@ -483,6 +523,9 @@ void eor_group_destroy(eor_group *g) {
     if (g->d_inst) (void)hipFree(g->d_inst);
     if (g->h_inst) (void)hipHostFree(g->h_inst);
     free_tasks(*g);
+    g->spread_tab.release();
+    g->spread_y.release();
+    g->prog.release();
     if (g->counter) (void)hipFree(g->counter);
     delete g;
 }

@@ -22,7 +22,7 @@ struct SpreadParams {
     unsigned int *counter;   // next unit; zero before and after a launch
     int32_t *prog;           // [ntask][n_max + SPREAD_EXTRA]; zero before and after a launch
     double2 *Lw;             // packed tiles of L, slot after slot
-    const int64_t *off;      // device [ntask]: first element of each slot, or NULL: slot * slot_elems
+    const longlong2 *off;    // device [ntask]: first element of each slot in Lw and in yw, or NULL: slot * slot_elems, * slot_y
     int64_t slot_elems;
     double2 *yw;             // per-slot w, then y
     int64_t slot_y;

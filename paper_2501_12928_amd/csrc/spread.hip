@@ -415,7 +415,8 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         const CallDesc C = a.call[inst];
         const int N = uniform(I.N), j = N - rem, i = j + u, stop = a.n_max;
         const double2 *A = uniform_ptr(I.A);
-        double2 *L = uniform_ptr(a.Lw + (a.off ? a.off[slot] : slot * a.slot_elems)), *yv = uniform_ptr(a.yw + slot * a.slot_y);
+        const longlong2 off = a.off ? a.off[slot] : make_longlong2(slot * a.slot_elems, slot * a.slot_y);
+        double2 *L = uniform_ptr(a.Lw + off.x), *yv = uniform_ptr(a.yw + off.y);
         int32_t *prog = uniform_ptr(a.prog + (int64_t)slot * (a.n_max + SPREAD_EXTRA));
         d4 xr[4], xi[4];
         if (u <= 1) __builtin_amdgcn_s_setprio(2);

@@ -39,3 +39,37 @@ def test_no_call_refused_for_the_spread_route():
     grp.close()
     for c in ctxs:
         c.close()
+
+
+def test_spread_memory_follows_each_theta_s_size():
+    """Batch sizes that change from call to call, small theta beside a large one:
+    every theta's bits are those of its own context, and the solve vectors of
+    4000 more small theta take what those theta need (4 KiB of solve vector and
+    progress words each at most), not the largest instance's size."""
+    import torch
+    import paper_2501_12928_amd as eor
+    ctxs = [_context(11, 2048), _context(12, 40), _context(13, 100)]
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    th = [-1.0 + 4.0 * torch.rand(b, 1, dtype=torch.float64, device="cuda", generator=gen) for b in (2, 4500, 60)]
+    alone = [c.loglike_batch(t)[0] for c, t in zip(ctxs, th)]
+    outs = [torch.empty_like(a) for a in alone]
+    infos = [torch.empty(a.shape, dtype=torch.int32, device="cuda") for a in alone]
+    grp = eor.Group(ctxs)
+    used = None
+    for sizes in ((1, 500, 7), (1, 4500, 7), (2, 300, 60), (0, 20, 3), (2, 4500, 60), (1, 500, 7)):
+        print(f"gpu: group of {sizes} theta", flush=True)
+        for o in outs:
+            o.fill_(7.0)
+        grp.loglike([t[:b] for t, b in zip(th, sizes)], outs=outs, infos=infos)
+        torch.cuda.synchronize()
+        for a, o, b in zip(alone, outs, sizes):
+            assert torch.equal(o[:b], a[:b]) and bool((o[b:] == 7.0).all())
+        free = torch.cuda.mem_get_info()[0]
+        if used is None:
+            used = free
+        else:
+            # the allocator hands out 2 MiB pieces: one more for each of four buffers
+            assert used - free <= 4000 * 4096 + (8 << 20), (used - free, sizes)
+    grp.close()
+    for c in ctxs:
+        c.close()
