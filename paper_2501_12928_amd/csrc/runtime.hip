@@ -75,6 +75,7 @@ struct eor_group {
     std::vector<int64_t> task_B, task_N; // B and tile rows per instance the task list was built for
     std::vector<int> order_N;            // the instances in list order, largest first
     unsigned int *counter = nullptr;
+    bool counter_clear = false;          // cleared before the first launch, left at zero by each
     double2 *Lw = nullptr;
     double2 *yw = nullptr;
     int64_t slots = 0, slot_tiles = 0, slot_y = 0;
@@ -383,6 +384,7 @@ eor::SpreadParams make_spread(const eor_group &g, const double *const *theta, do
 // (whose A the launch reads until then).
 eor_status record_call(eor_group &g, hipStream_t s) {
     hipError_t e = g.order.leave(s);
+    g.counter_clear = g.counter_clear || e == hipSuccess;
     for (size_t i = 0; i < g.inst.size() && e == hipSuccess; ++i) e = g.inst[i]->c.order.leave(s);
     return e == hipSuccess ? EOR_OK : eor::hip_status(e, "hipEventRecord");
 }
@@ -411,6 +413,7 @@ eor_status run_group(eor_group &g, const int64_t *B, const double *const *theta,
         g.h_inst[i].ts = g.ts_bucket[eor::bucket_index(g.inst[i]->c.n)];
     }
     e = hipMemcpyAsync(g.d_inst, g.h_inst, g.inst.size() * sizeof(eor::InstDesc), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && !g.counter_clear) e = hipMemsetAsync(g.counter, 0, sizeof(unsigned int), s);
     if (e != hipSuccess) return eor::hip_status(e, "instance descriptors");
     const int64_t resident = eor::resident_per_cu(t) * g.num_cu;
     const int64_t want = std::min<int64_t>(g.ntask, resident);
@@ -503,8 +506,6 @@ eor_status eor_group_create(int32_t n_inst, eor_ctx *const *insts, eor_group **o
     hipError_t e = hipMalloc(&g->d_inst, n_inst * sizeof(eor::InstDesc));
     if (e == hipSuccess) e = hipHostMalloc((void **)&g->h_inst, n_inst * sizeof(eor::InstDesc));
     if (e == hipSuccess) e = hipMalloc(&g->counter, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipMemset(g->counter, 0, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         eor_group_destroy(g);
         return eor::hip_status(e, "eor_group_create");

@@ -73,3 +73,28 @@ def test_spread_memory_follows_each_theta_s_size():
     grp.close()
     for c in ctxs:
         c.close()
+
+
+def test_creating_a_group_does_not_wait_for_the_device():
+    """A group is created while another stream has a second of work queued."""
+    import torch
+    import paper_2501_12928_amd as eor
+    ctxs = [_context(21, 70), _context(22, 40)]
+    gen = torch.Generator(device="cuda").manual_seed(23)
+    th = [-1.0 + 4.0 * torch.rand(b, 1, dtype=torch.float64, device="cuda", generator=gen) for b in (3, 5)]
+    alone = [c.loglike_batch(t)[0] for c, t in zip(ctxs, th)]
+    torch.cuda.synchronize()
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    print("gpu: a group beside a busy stream", flush=True)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(1_000_000_000)
+        done.record()
+    grp = eor.Group(ctxs)
+    assert not done.query()
+    torch.cuda.synchronize()
+    outs, infos = grp.loglike(th)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, a) for o, a in zip(outs, alone))
+    grp.close()
+    for c in ctxs:
+        c.close()
