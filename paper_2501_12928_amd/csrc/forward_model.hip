@@ -130,7 +130,10 @@ __device__ __forceinline__ double2 phase(const Pix &x, bool in, double fc, doubl
 // the last a row of zeros of S, so they add nothing.
 // S goes from L2 straight to the operand registers, three steps ahead; only the
 // phase factors, which are made once for all waves, pass through LDS, in stages
-// of 32 pixels with one barrier each. (With both staged through LDS, 16 pixels
+// of 32 pixels with one barrier each; chunks are cut in units of 16 pixels, and
+// one that ends with half a stage stops there (all 32 pixels of a last stage
+// multiplied took 49 us in place of 33 for 3200 x 144 cells from 144 pixels in
+// chunks of 16). (With both staged through LDS, 16 pixels
 // and two barriers a stage, the waves of a workgroup held each other up: matrix
 // cores busy 71% of a counter run, 1.19 ms for 20000 x 4096. Now 77%, 1.11 ms; at
 // the clock it runs at, 2.1 GHz, the products alone take 0.94 ms. Two LDS buffers of
@@ -183,6 +186,7 @@ __global__ __launch_bounds__(256, 2) void fm_partial_kernel(FmArgs a) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
+        if (8 * i == FC && pbeg + FC >= pend) break;
         Es[0][eb][ep + 8 * i] = phase(x[i], pbeg + ep + 8 * i < pend, fc, bx, by, turn);
         x[i] = load_pix(a, pbeg + FK + ep + 8 * i, lm2, beam);
     }
@@ -197,6 +201,7 @@ __global__ __launch_bounds__(256, 2) void fm_partial_kernel(FmArgs a) {
     for (int64_t p0 = pbeg; p0 < pend; p0 += FK, buf ^= 1) {
 #pragma unroll
         for (int u = 0; u < FK / 4; ++u) {
+            if (u == FC / 4 && p0 + FC >= pend) break;  // a chunk may end with half a stage (uniform)
             load_s(a, sb[(u + AHEAD) % (AHEAD + 1)], p0 + 4 * (u + AHEAD), voff);
             __builtin_amdgcn_sched_barrier(0);
             const double2 av = Es[buf][wr + l16][4 * u + q];

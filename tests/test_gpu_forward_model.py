@@ -108,3 +108,29 @@ def test_likelihood_through_forward_model():
     assert np.all(info.cpu().numpy() == 0)
     assert np.all(np.abs(logL - ref) <= tol(ref))
     ctx.close()
+
+
+def test_half_stages_are_not_multiplied():
+    """Chunks are cut in units of 16 pixels, stages hold 32: 16 chunks of 48 pixels
+    take three quarters of the products of 16 chunks of 64, and the same writes."""
+    import torch
+    import paper_2501_12928_amd as eor
+    rng = np.random.default_rng(7)
+
+    def us(n_pix):
+        args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in _random_instrument(rng, 16, 256, n_pix, 128, 1)]
+        out = eor.forward_model(*args, 1.0)
+        best = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda._sleep(200000)   # the launches are queued behind it, so that the host is not timed
+            a.record()
+            eor.forward_model(*args, 1.0, out=out)
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b) * 1e3)
+        return min(best)
+
+    print("gpu: forward model, 768 and 1024 pixels", flush=True)
+    t48, t64 = us(16 * 48), us(16 * 64)
+    assert t48 < 0.92 * t64, (t48, t64)
