@@ -134,3 +134,16 @@ def test_half_stages_are_not_multiplied():
     print("gpu: forward model, 768 and 1024 pixels", flush=True)
     t48, t64 = us(16 * 48), us(16 * 64)
     assert t48 < 0.92 * t64, (t48, t64)
+
+
+@pytest.mark.parametrize("n_pix", [33, 129, 144, 160])
+def test_chunks_of_two_units_where_the_chip_is_full(n_pix):
+    """Sizes whose chunks would hold 16 pixels and fill the chip several times; the
+    bound is that of test_forward_model_pixel_counts."""
+    import paper_2501_12928_amd as eor
+    rng = np.random.default_rng(n_pix)
+    freq, bl, lm, beam, uv, Z = _random_instrument(rng, 16, 200, n_pix, 129, 1)
+    ref = fm.forward_model(freq, bl, lm, beam, uv, Z, 1.0)
+    print(f"gpu: forward model, full chip, n_pix={n_pix}", flush=True)
+    got = eor.forward_model(freq, bl, lm, beam, uv, Z, 1.0).cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= 1e-13 * n_pix * beam.max() * np.abs(Z).max()
