@@ -272,11 +272,17 @@ __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
                 for (int t = 0; t < 4; ++t) acc[rt][c] = mfma32(hv[t], w[c][t], acc[rt][c]);
         }
     };
+    // Forward only, loads stay in front of the next group's products: moved behind
+    // them by the compiler they were waited for at once, and widths of 388 to 448
+    // needed registers that left one wave per SIMD in place of two (16384 samples of
+    // five members, width 448: 517 us, 390 like this; 512: 653 and 592; 256: 172 and 160).
     for (int g = 0; g < HK; g += 32) {
         step2(g, wv);
         load_w2(g + 32, wv);
+        if constexpr (!BWD) __builtin_amdgcn_sched_barrier(0);
         step2(g + 16, wb);
         load_w2(g + 48, wb);
+        if constexpr (!BWD) __builtin_amdgcn_sched_barrier(0);
     }
     // output f[s] = sum_o GELU(Z2[s][o]) W3[o] + b3: this wave's units, then
     // the 16 lanes of a group (fixed xor tree), then the waves in order
