@@ -153,23 +153,6 @@ eor_status ensure_work(Context &c, int64_t want) {
     return fail(EOR_ERR_OOM, "cannot allocate the per-theta workspace");
 }
 
-// Of a call of B theta in rounds of `round` (the resident workgroups, or the
-// slots if they are fewer), how many of the last ones to spread over all
-// workgroups: of a whole round and of what is left after whole rounds, those
-// that the estimates say are sooner done so. 32-wide tiles sum in another
-// order and are never spread.
-int64_t spread_count(const Context &c, int64_t B, int64_t round) {
-    if (c.tune.ts != eor::TS) return 0;
-    auto better = [&](int64_t n) {
-        const double lone = eor::lone_us(c.N) * (1.0 + 0.15 * std::min<double>(1.0, (double)n / c.num_cu));
-        return n > 0 && eor::spread_us(eor::spread_chain_us(c.N), n * eor::spread_work_us(c.N), c.N) < 0.97 * lone &&
-               n * eor::n_tiles(c.N) < ((int64_t)1 << 31) - 4096;
-    };
-    if (B >= round && better(round)) return B;
-    const int64_t rest = B % round;
-    return better(rest) ? rest : 0;
-}
-
 }  // namespace
 
 extern "C" {
@@ -380,7 +363,8 @@ static eor_status loglike_impl(eor_ctx *ctx, int64_t B, const double *theta, dou
     if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
     // Whole rounds of one theta per workgroup, and a call or remainder that
     // would leave most of the GPU idle spread over all workgroups.
-    const int64_t lone = B - spread_count(c, B, grid);
+    // 32-wide tiles sum in another order and are never spread.
+    const int64_t lone = B - (c.tune.ts == eor::TS ? eor::spread_count(c.N, B, grid, c.num_cu) : 0);
     if (lone > 0) {
         eor::LikeParams p;
         std::memset(&p, 0, sizeof(p));

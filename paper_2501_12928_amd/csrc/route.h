@@ -1,0 +1,67 @@
+// Which theta of a call are spread over all workgroups (spread.hip) and which
+// have a workgroup of their own (likelihood.hip). The results are the same bits
+// either way, so the choice is by time alone; host code without HIP.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace eor {
+
+// Estimated times (us) on 256 CUs, N the 64-wide tile rows. Measured at n = 50 to
+// 1010 (N = 1 .. 16) with 1 to 256 theta, where all are within 13% (N = 2; else
+// 9%), and at N = 24, 32, 47 and 64 with up to 64 theta (10%).
+//
+// One workgroup takes a theta in lone_us, more the more of the CUs have one
+// (load, 0 to 1): N = 1 30 us, of 256 at a time 48; N = 4 168 and 230; N = 8 753 and
+// 878; N = 16 4609 and 4950; N = 64 253 and 297 ms.
+inline double lone_us(int64_t N, double load) {
+    const double n = (double)N, n3 = n * n * n;
+    return 8.0 + 17.0 * n + 2.2 * n * n + 0.92 * n3 + load * (16.0 * n + 0.149 * std::min(1.0, n / 32.0) * n3);
+}
+
+// Spread, a theta's diagonal tiles follow one another every 27 us, and its N (N +
+// 1) / 2 tiles take the whole GPU 0.08 us each plus their products at 78 TFLOP/s.
+inline double spread_chain_us(int64_t N) { return 27.0 * N; }
+inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 * 262144.0 * N * N * N / 78e6; }
+
+// The chain and the work of all theta overlap the better the more tile rows there
+// are: (chain^p + work^p)^(1/p), with p from 1.2 (nearly their sum: there is too
+// little of either to fill the other's gaps) to large (the longer of the two).
+// One tile row is one unit, which waits for nothing. Fitted, p is 1.1 to 1.3 at N
+// = 2 to 4, 1.4 at 5, 1.85 at 8, 2.2 at 11 and 2.95 at 16.
+inline double spread_us(double chain, double work, int64_t N) {
+    const double p = N == 1 ? 3.0 : std::max(1.2, 0.8 + 0.125 * (double)N);
+    const double a = std::max(chain, work), b = std::min(chain, work);
+    return a * std::pow(1.0 + std::pow(b / a, p), 1.0 / p);
+}
+
+// Where the chain bounds, one workgroup per CU: a second one's matrix
+// instructions hold up the single wave that factors a diagonal tile (19 us
+// beside them, 14 alone). With much more work than chain, two, so that one
+// computes while the other waits. The line, as work over chain, rises with the
+// tile rows N, since longer sums leave less waiting to cover. Measured, one
+// against two per CU: N = 4, 64 theta (work 0.6 times the chain) 164 / 162 us; N = 9,
+// 32 (0.9) 364 / 378, 40 (1.1) 415 / 388; N = 16, 14 (1.0) 550 / 638, 24 (1.6) 859 /
+// 744; N = 24, 10 (1.3) 932 / 1022, 12 (1.6) 1129 / 1092; N = 32, 8 (1.8) 1531 /
+// 1563, 10 (2.2) 1955 / 1830; N = 47, 4 (1.8) 2.21 / 2.37 ms, 6 (2.6) 3.19 / 3.18; N =
+// 64, two (1.6) 2.64 / 3.06, four (3.1) 4.94 / 5.12.
+inline int spread_per_cu(double chain, double work, int64_t N) { return work < (0.5 + N / 22.0) * chain ? 1 : 2; }
+
+// Of a call of B theta in rounds of `round` (the resident workgroups, or the
+// slots if they are fewer), how many of the last ones to spread: of a whole round
+// and of what is left after whole rounds, those that the estimates say are sooner
+// done so.
+inline int64_t spread_count(int64_t N, int64_t B, int64_t round, int num_cu) {
+    auto better = [&](int64_t n) {
+        const double lone = lone_us(N, std::min<double>(1.0, (double)n / num_cu));
+        return n > 0 && spread_us(spread_chain_us(N), n * spread_work_us(N), N) < 0.97 * lone &&
+               n * (N * (N + 1) / 2) < ((int64_t)1 << 31) - 4096;
+    };
+    if (B >= round && better(round)) return B;
+    const int64_t rest = B % round;
+    return better(rest) ? rest : 0;
+}
+
+}  // namespace eor

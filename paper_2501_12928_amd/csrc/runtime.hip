@@ -171,7 +171,7 @@ void free_tasks(eor_group &g) {
 void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
     const int64_t n = (int64_t)tasks.size(), N_max = g.inst[tasks[0].x]->c.N;
     double chain = 0.0, work = 0.0;
-    const double load = 1.0 + 0.15 * std::min(1.0, (double)n / g.num_cu);
+    const double load = std::min(1.0, (double)n / g.num_cu);
     std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
     for (int i = 0; i < g.num_cu; ++i) busy.push(0.0);
     int64_t elems = 0, y_elems = 0, units = 0;
@@ -180,7 +180,7 @@ void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
         const int64_t N = g.inst[tasks[t].x]->c.N;
         chain = std::max(chain, eor::spread_chain_us(N));
         work += eor::spread_work_us(N);
-        const double end = busy.top() + load * eor::lone_us(N);
+        const double end = busy.top() + eor::lone_us(N, load);
         busy.pop();
         busy.push(end);
         g.est_lone = std::max(g.est_lone, end);

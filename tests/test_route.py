@@ -1,0 +1,89 @@
+"""The rule that spreads a call's theta over all workgroups or gives each a
+workgroup of its own (csrc/route.h), against measured times of both routes. Host
+code, compiled here by itself."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2501_12928_amd", "csrc")
+CU = 256
+
+# Measured on one MI355X, us: tile rows -> theta -> (one workgroup each, spread),
+# at n = 64, 128, 178, 242, 320, 370, 434, 512, 562, 690 and 1010.
+MEASURED = {
+    1: {1: (30, 27), 16: (31, 28), 32: (32, 28), 48: (33, 28), 64: (35, 28), 90: (36, 29), 110: (38, 30),
+        128: (39, 30), 160: (41, 31), 200: (44, 31), 230: (46, 32), 256: (48, 32)},
+    2: {1: (59, 54), 16: (60, 55), 32: (62, 58), 48: (64, 60), 64: (66, 64), 90: (69, 75), 110: (71, 86),
+        128: (73, 91), 160: (77, 97), 200: (83, 111), 230: (87, 116), 256: (90, 120)},
+    3: {1: (103, 80), 16: (104, 84), 32: (106, 90), 48: (109, 99), 64: (112, 106), 90: (117, 125), 110: (121, 137),
+        128: (122, 142), 160: (130, 162), 200: (138, 179), 230: (145, 196), 256: (149, 211)},
+    4: {1: (168, 106), 16: (170, 114), 32: (174, 128), 48: (177, 131), 64: (181, 157), 90: (189, 175),
+        110: (194, 194), 128: (198, 212), 160: (206, 239), 200: (215, 279), 230: (223, 306), 256: (230, 329)},
+    5: {1: (258, 131), 16: (262, 142), 32: (266, 152), 48: (271, 177), 64: (275, 209), 90: (283, 238),
+        110: (289, 263), 128: (294, 292), 160: (303, 335), 200: (315, 406), 230: (324, 452), 256: (334, 493)},
+    6: {1: (383, 156), 16: (387, 168), 32: (395, 186), 48: (400, 238), 64: (404, 267), 90: (412, 309),
+        110: (420, 352), 128: (426, 393), 160: (436, 456), 200: (451, 567), 230: (464, 634), 256: (472, 696)},
+    7: {1: (542, 182), 16: (553, 195), 32: (559, 219), 48: (564, 296), 64: (567, 329), 90: (577, 398),
+        110: (584, 463), 128: (591, 512), 160: (603, 610), 200: (622, 780), 230: (642, 905), 256: (655, 1035)},
+    8: {1: (753, 207), 16: (757, 227), 32: (769, 284), 48: (775, 354), 64: (777, 402), 90: (785, 503),
+        110: (795, 588), 128: (800, 666), 160: (820, 808), 200: (844, 1071), 230: (862, 1272), 256: (878, 1432)},
+    9: {1: (1007, 233), 16: (1015, 254), 32: (1027, 351), 48: (1028, 421), 64: (1035, 492), 90: (1044, 630),
+        110: (1055, 740), 128: (1069, 860), 160: (1086, 1085), 200: (1109, 1450), 230: (1130, 1679),
+        256: (1153, 1896)},
+    11: {1: (1685, 285), 16: (1695, 321), 32: (1706, 485), 48: (1719, 575), 64: (1717, 720), 90: (1735, 955),
+         110: (1749, 1213), 128: (1756, 1438), 160: (1781, 1853), 200: (1807, 2357), 230: (1844, 2710),
+         256: (1891, 3047)},
+    16: {1: (4609, 414), 16: (4624, 595), 32: (4641, 907), 48: (4665, 1322), 64: (4681, 1761), 90: (4714, 2561),
+         110: (4722, 3146), 128: (4743, 3691), 160: (4772, 4660), 200: (4818, 5864), 230: (4947, 6801)},
+}
+
+SHIM = """
+#include "route.h"
+extern "C" {
+double lone(long N, double load) { return eor::lone_us(N, load); }
+double spread(long N, long B) { return eor::spread_us(eor::spread_chain_us(N), B * eor::spread_work_us(N), N); }
+long count(long N, long B, long round, int cu) { return eor::spread_count(N, B, round, cu); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("route")
+    (d / "route.cpp").write_text(SHIM)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "route.so"),
+                    str(d / "route.cpp")], check=True)
+    lib = ctypes.CDLL(str(d / "route.so"))
+    lib.lone.restype = lib.spread.restype = ctypes.c_double
+    lib.lone.argtypes = [ctypes.c_long, ctypes.c_double]
+    lib.spread.argtypes = [ctypes.c_long, ctypes.c_long]
+    lib.count.restype = ctypes.c_long
+    lib.count.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_long, ctypes.c_int]
+    return lib
+
+
+@pytest.mark.parametrize("N", sorted(MEASURED))
+def test_estimates_and_choice(route, N):
+    """Both estimates within 15% of what was measured, and the chosen route at most
+    5% slower than the other."""
+    for B, (lone, spread) in MEASURED[N].items():
+        assert abs(route.lone(N, B / CU) / lone - 1) <= 0.15, (B, route.lone(N, B / CU), lone)
+        assert abs(route.spread(N, B) / spread - 1) <= 0.15, (B, route.spread(N, B), spread)
+        # a call of B theta is one round of at most 256
+        n = route.count(N, B, min(B, CU), CU)
+        assert n in (0, B)
+        assert (spread if n else lone) <= 1.05 * min(lone, spread), (B, n, lone, spread)
+
+
+def test_estimates_follow_the_size(route):
+    """No size at which the number of theta that are spread jumps: it falls slowly
+    from the smallest tile rows to a few and rises from there."""
+    most = {N: max([B for B in range(1, CU) if route.count(N, B, B, CU)], default=0) for N in range(2, 65)}
+    for N in range(2, 64):
+        assert abs(most[N + 1] - most[N]) <= 30, (N, most[N], most[N + 1])
