@@ -50,18 +50,25 @@ inline double spread_us(double chain, double work, int64_t N) {
 inline int spread_per_cu(double chain, double work, int64_t N) { return work < (0.5 + N / 22.0) * chain ? 1 : 2; }
 
 // Of a call of B theta in rounds of `round` (the resident workgroups, or the
-// slots if they are fewer), how many of the last ones to spread: of a whole round
-// and of what is left after whole rounds, those that the estimates say are sooner
-// done so.
+// slots if they are fewer), how many of the last ones to spread: none, what is left
+// after whole rounds, or all. Spread, every round is a launch that ends before the
+// next begins; with a workgroup each, one launch takes all rounds and a workgroup
+// goes on to its next theta at once, so that a further round costs little more
+// than one theta's time and a last partial round some us less than by itself. All
+// rounds are spread where the rounds are small (slots for a few theta: 100 theta at
+// n = 1000 in rounds of 10, 4.9 ms against 60), or at one tile row up to about 2000
+// theta: 1000 theta at n = 64 121 us against 150, 2000 237 and 252, 5000 590 and
+// 556.
 inline int64_t spread_count(int64_t N, int64_t B, int64_t round, int num_cu) {
-    auto better = [&](int64_t n) {
-        const double lone = lone_us(N, std::min<double>(1.0, (double)n / num_cu));
-        return n > 0 && spread_us(spread_chain_us(N), n * spread_work_us(N), N) < 0.97 * lone &&
-               n * (N * (N + 1) / 2) < ((int64_t)1 << 31) - 4096;
-    };
-    if (B >= round && better(round)) return B;
-    const int64_t rest = B % round;
-    return better(rest) ? rest : 0;
+    auto spread = [&](int64_t n) { return n ? spread_us(spread_chain_us(N), n * spread_work_us(N), N) : 0.0; };
+    auto lone = [&](int64_t n) { return n ? lone_us(N, std::min<double>(1.0, (double)n / num_cu)) : 0.0; };
+    if (std::min(B, round) * (N * (N + 1) / 2) >= ((int64_t)1 << 31) - 4096) return 0;  // the units of a launch
+    const int64_t rounds = B / round, rest = B % round;
+    if (rounds == 0) return spread(rest) < 0.97 * lone(rest) ? rest : 0;
+    const double tail = rest ? lone(rest) - 4.0 * N : 0.0, part = rest ? spread(rest) + 3.0 : 0.0;
+    const double whole = lone(round) + (rounds - 1) * (lone_us(N, 0.0) - 4.0) + std::min(tail, part);
+    if (rounds * spread(round) + spread(rest) < 0.97 * whole) return B;
+    return part < tail ? rest : 0;
 }
 
 }  // namespace eor
