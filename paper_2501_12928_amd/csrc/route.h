@@ -6,6 +6,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <functional>
+#include <queue>
+#include <vector>
 
 namespace eor {
 
@@ -69,6 +72,42 @@ inline int64_t spread_count(int64_t N, int64_t B, int64_t round, int num_cu) {
     const double whole = lone(round) + (rounds - 1) * (lone_us(N, 0.0) - 4.0) + std::min(tail, part);
     if (rounds * spread(round) + spread(rest) < 0.97 * whole) return B;
     return part < tail ? rest : 0;
+}
+
+// Theta of one size in a group: tile rows and how many.
+struct Sizes {
+    int64_t N, count;
+};
+
+// Estimated time (us) of a group with a workgroup per theta, the sizes largest
+// first: the longest of num_cu workgroups that each take the next theta when they
+// are done. Beyond 8192 theta the mean load, or the longest theta, which many small
+// ones fill up evenly (the schedule itself took the host 1 ms for 100000 theta).
+inline double lone_group_us(const std::vector<Sizes> &sizes, int num_cu) {
+    int64_t n = 0;
+    for (const Sizes &s : sizes) n += s.count;
+    const double load = std::min(1.0, (double)n / num_cu);
+    double sum = 0.0, longest = 0.0;
+    for (const Sizes &s : sizes) {
+        if (s.count < 1) continue;
+        const double us = lone_us(s.N, load);
+        sum += s.count * us;
+        longest = std::max(longest, us);
+    }
+    if (n > 8192) return std::max(longest, sum / num_cu);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+    for (int i = 0; i < num_cu; ++i) busy.push(0.0);
+    double end = 0.0;
+    for (const Sizes &s : sizes) {
+        const double us = lone_us(s.N, load);
+        for (int64_t b = 0; b < s.count; ++b) {
+            const double t = busy.top() + us;
+            busy.pop();
+            busy.push(t);
+            end = std::max(end, t);
+        }
+    }
+    return end;
 }
 
 }  // namespace eor

@@ -12,7 +12,6 @@
 #include <iterator>
 #include <map>
 #include <new>
-#include <queue>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -168,33 +167,27 @@ void free_tasks(eor_group &g) {
 // Whether spreading every theta of the task list over all workgroups is sooner
 // done by the estimates (few theta, or few large ones that would keep one
 // workgroup each busy long after the others are done), and what it needs.
-void plan_spread(eor_group &g, const std::vector<int2> &tasks) {
-    const int64_t n = (int64_t)tasks.size(), N_max = g.inst[tasks[0].x]->c.N;
+void plan_spread(eor_group &g) {
+    std::vector<eor::Sizes> sizes;
     double chain = 0.0, work = 0.0;
-    const double load = std::min(1.0, (double)n / g.num_cu);
-    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
-    for (int i = 0; i < g.num_cu; ++i) busy.push(0.0);
-    int64_t elems = 0, y_elems = 0, units = 0;
-    g.est_lone = 0.0;
-    for (int64_t t = 0; t < n; ++t) {
-        const int64_t N = g.inst[tasks[t].x]->c.N;
+    int64_t N_max = 0;
+    g.spread_elems = g.spread_y_elems = g.spread_units = 0;
+    for (int i : g.order_N) {
+        const int64_t N = g.task_N[i], B = g.task_B[i];
+        if (B < 1) continue;
+        sizes.push_back({N, B});
+        N_max = std::max(N_max, N);
         chain = std::max(chain, eor::spread_chain_us(N));
-        work += eor::spread_work_us(N);
-        const double end = busy.top() + eor::lone_us(N, load);
-        busy.pop();
-        busy.push(end);
-        g.est_lone = std::max(g.est_lone, end);
-        elems += eor::n_tiles(N) * eor::TS2;
-        y_elems += N * eor::TS;
-        units += eor::n_tiles(N);
+        work += B * eor::spread_work_us(N);
+        g.spread_units += B * eor::n_tiles(N);
+        g.spread_y_elems += B * N * eor::TS;
     }
+    g.spread_elems = g.spread_units * eor::TS2;
+    g.spread_rows = N_max;
+    g.est_lone = eor::lone_group_us(sizes, g.num_cu);
     g.est_spread = eor::spread_us(chain, work, N_max);
     g.spread_per_cu = eor::spread_per_cu(chain, work, N_max);
-    g.spread_rows = N_max;
-    g.spread_elems = elems;
-    g.spread_y_elems = y_elems;
-    g.spread_units = units;
-    if (!(g.est_spread < 0.97 * g.est_lone) || units >= ((int64_t)1 << 31) - 4096) g.est_spread = INFINITY;
+    if (!(g.est_spread < 0.97 * g.est_lone) || g.spread_units >= ((int64_t)1 << 31) - 4096) g.est_spread = INFINITY;
 }
 
 // The memory of a planned spread launch: false if it cannot be had. The launch
@@ -271,7 +264,7 @@ eor_status build_tasks(eor_group &g, const int64_t *B) {
         free_tasks(g);
         return eor::hip_status(e, "task list");
     }
-    plan_spread(g, tasks);
+    plan_spread(g);
     return EOR_OK;
 }
 

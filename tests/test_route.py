@@ -2,9 +2,11 @@
 workgroup of its own (csrc/route.h), against measured times of both routes. Host
 code, compiled here by itself."""
 import ctypes
+import heapq
 import os
 import shutil
 import subprocess
+import time
 
 import pytest
 
@@ -77,6 +79,11 @@ SHIM = """
 extern "C" {
 double lone(long N, double load) { return eor::lone_us(N, load); }
 double spread(long N, long B) { return eor::spread_us(eor::spread_chain_us(N), B * eor::spread_work_us(N), N); }
+double group(const long *N, const long *count, int n, int cu) {
+    std::vector<eor::Sizes> s;
+    for (int i = 0; i < n; ++i) s.push_back({N[i], count[i]});
+    return eor::lone_group_us(s, cu);
+}
 long count(long N, long B, long round, int cu) { return eor::spread_count(N, B, round, cu); }
 }
 """
@@ -95,6 +102,7 @@ def route(tmp_path_factory):
     lib.lone.restype = lib.spread.restype = ctypes.c_double
     lib.lone.argtypes = [ctypes.c_long, ctypes.c_double]
     lib.spread.argtypes = [ctypes.c_long, ctypes.c_long]
+    lib.group.restype = ctypes.c_double
     lib.count.restype = ctypes.c_long
     lib.count.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_long, ctypes.c_int]
     return lib
@@ -138,3 +146,40 @@ def test_one_tile_row_in_one_launch(route):
     for B in (5000, 20000, 100000, 5000000):
         assert route.count(1, B, CU, CU) <= B % CU
     assert route.count(1, 512, CU, CU) == 512
+
+
+def _group(route, sizes):
+    N = (ctypes.c_long * len(sizes))(*[n for n, _ in sizes])
+    c = (ctypes.c_long * len(sizes))(*[b for _, b in sizes])
+    return route.group(N, c, len(sizes), CU)
+
+
+@pytest.mark.parametrize("sizes", [
+    [(5, 3)], [(32, 1), (1, 5000)], [(64, 2), (9, 300), (2, 40)], [(64, 1), (1, 20000)], [(32, 40), (9, 300), (3, 9000)],
+    [(8, 0), (4, 200), (1, 0)], [(7, 8192)], [(7, 8193)],
+])
+def test_group_estimate_is_its_schedule(route, sizes):
+    """Within 5% of a schedule in which each workgroup takes the next theta, also
+    where the estimate does not play it through."""
+    n = sum(b for _, b in sizes)
+    busy = [0.0] * CU
+    for N, b in sizes:
+        for _ in range(b):
+            heapq.heapreplace(busy, busy[0] + route.lone(N, min(1.0, n / CU)))
+    assert abs(_group(route, sizes) / max(busy) - 1) <= 0.05
+
+
+def test_group_estimate_is_quick(route):
+    """The batch sizes of a group may change with every call: five million theta are
+    estimated in less than the 10 ms that 100000 take the GPU."""
+    t = time.perf_counter()
+    assert _group(route, [(64, 1), (1, 5000000)]) > 0
+    assert time.perf_counter() - t < 10e-3
+
+
+def test_full_rounds_have_a_workgroup_each(route):
+    """512 theta of two tile rows or more, in rounds of 256 or 512, are not spread:
+    tests that mean the kernel with one workgroup per theta take that many."""
+    for N in range(2, 65):
+        assert route.count(N, 512, 256, CU) == 0 and route.count(N, 512, 512, CU) == 0
+    assert route.count(1, 5120, 256, CU) == 0 and route.count(1, 5120, 512, CU) == 0
