@@ -197,30 +197,38 @@ __global__ __launch_bounds__(256, 2) void fm_partial_kernel(FmArgs a) {
     }
     __syncthreads();
     int buf = 0;
-#pragma unroll 1
-    for (int64_t p0 = pbeg; p0 < pend; p0 += FK, buf ^= 1) {
-#pragma unroll
-        for (int u = 0; u < FK / 4; ++u) {
-            if (u == FC / 4 && p0 + FC >= pend) break;  // a chunk may end with half a stage (uniform)
+    // Step u of the stage from p0; in a full stage, the phase factors of the next.
+    auto step = [&](int64_t p0, int u, bool full) __attribute__((always_inline)) {
+        if (full || u < FC / 4 - AHEAD) {
             load_s(a, sb[(u + AHEAD) % (AHEAD + 1)], p0 + 4 * (u + AHEAD), voff);
             __builtin_amdgcn_sched_barrier(0);
-            const double2 av = Es[buf][wr + l16][4 * u + q];
-            const double as = av.x + av.y;
-            const SStep &s = sb[u % (AHEAD + 1)];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                t1[c] = mfma64(av.x, s.v[c].x, t1[c]);
-                t2[c] = mfma64(av.y, s.v[c].y, t2[c]);
-                t3[c] = mfma64(as, s.v[c].x + s.v[c].y, t3[c]);
-            }
-            if (u % 2 == 1) {
-                const int64_t p = p0 + FK + ep + 4 * (u - 1);
-                Es[buf ^ 1][eb][ep + 4 * (u - 1)] = phase(x[u / 2], p < pend, fc, bx, by, turn);
-                x[u / 2] = load_pix(a, p + FK, lm2, beam);
-            }
-            __builtin_amdgcn_sched_barrier(0);
         }
+        const double2 av = Es[buf][wr + l16][4 * u + q];
+        const double as = av.x + av.y;
+        const SStep &s = sb[u % (AHEAD + 1)];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            t1[c] = mfma64(av.x, s.v[c].x, t1[c]);
+            t2[c] = mfma64(av.y, s.v[c].y, t2[c]);
+            t3[c] = mfma64(as, s.v[c].x + s.v[c].y, t3[c]);
+        }
+        if (full && u % 2 == 1) {
+            const int64_t p = p0 + FK + ep + 4 * (u - 1);
+            Es[buf ^ 1][eb][ep + 4 * (u - 1)] = phase(x[u / 2], p < pend, fc, bx, by, turn);
+            x[u / 2] = load_pix(a, p + FK, lm2, beam);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int64_t p0 = pbeg;
+#pragma unroll 1
+    for (; p0 + FC < pend; p0 += FK, buf ^= 1) {
+#pragma unroll
+        for (int u = 0; u < FK / 4; ++u) step(p0, u, true);
         __syncthreads();
+    }
+    if (p0 < pend) {  // a chunk may end with half a stage
+#pragma unroll
+        for (int u = 0; u < FC / 4; ++u) step(p0, u, false);
     }
     // lane holds G[b0 + wr + q + 4 r][k0 + wc + 16 c + l16]:
     // re = T1 - T2, im = T3 - T1 - T2
