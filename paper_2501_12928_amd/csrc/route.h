@@ -13,15 +13,15 @@
 namespace eor {
 
 // Estimated times (us) on 256 CUs, N the 64-wide tile rows. Measured at n = 50 to
-// 1010 (N = 1 .. 16) with 1 to 256 theta, where all are within 13% (N = 2; else
-// 9%), and at N = 24, 32, 47 and 64 with up to 64 theta (10%).
+// 1010 (N = 1 .. 16) with 1 to 256 theta, where all are within 13% (spread, N = 1 and
+// 2; else 9%), and at N = 24, 32, 47 and 64 with up to 64 theta (10%).
 //
 // One workgroup takes a theta in lone_us, more the more of the CUs have one
 // (load, 0 to 1): N = 1 30 us, of 256 at a time 48; N = 4 168 and 230; N = 8 753 and
 // 878; N = 16 4609 and 4950; N = 64 253 and 297 ms.
 inline double lone_us(int64_t N, double load) {
     const double n = (double)N, n3 = n * n * n;
-    return 8.0 + 17.0 * n + 2.2 * n * n + 0.92 * n3 + load * (16.0 * n + 0.149 * std::min(1.0, n / 32.0) * n3);
+    return 10.0 + 17.0 * n + 2.2 * n * n + 0.92 * n3 + load * (16.0 * n + 0.149 * std::min(1.0, n / 32.0) * n3);
 }
 
 // Spread, a theta's diagonal tiles follow one another every 27 us, and its N (N +
@@ -35,7 +35,7 @@ inline double spread_work_us(int64_t N) { return 0.04 * N * (N + 1) + 4.0 / 3.0 
 // One tile row is one unit, which waits for nothing. Fitted, p is 1.1 to 1.3 at N
 // = 2 to 4, 1.4 at 5, 1.85 at 8, 2.2 at 11 and 2.95 at 16.
 inline double spread_us(double chain, double work, int64_t N) {
-    const double p = N == 1 ? 3.0 : std::max(1.2, 0.8 + 0.125 * (double)N);
+    const double p = N == 1 ? 4.0 : std::max(1.2, 0.8 + 0.125 * (double)N);
     const double a = std::max(chain, work), b = std::min(chain, work);
     return a * std::pow(1.0 + std::pow(b / a, p), 1.0 / p);
 }
@@ -66,11 +66,11 @@ inline int64_t spread_count(int64_t N, int64_t B, int64_t round, int num_cu) {
     auto spread = [&](int64_t n) { return n ? spread_us(spread_chain_us(N), n * spread_work_us(N), N) : 0.0; };
     auto lone = [&](int64_t n) { return n ? lone_us(N, std::min<double>(1.0, (double)n / num_cu)) : 0.0; };
     if (std::min(B, round) * (N * (N + 1) / 2) >= ((int64_t)1 << 31) - 4096) return 0;  // the units of a launch
+    if (B <= round) return spread(B) < 0.97 * lone(B) ? B : 0;
     const int64_t rounds = B / round, rest = B % round;
-    if (rounds == 0) return spread(rest) < 0.97 * lone(rest) ? rest : 0;
     const double tail = rest ? lone(rest) - 4.0 * N : 0.0, part = rest ? spread(rest) + 3.0 : 0.0;
-    const double whole = lone(round) + (rounds - 1) * (lone_us(N, 0.0) - 4.0) + std::min(tail, part);
-    if (rounds * spread(round) + spread(rest) < 0.97 * whole) return B;
+    const double whole = lone(round) + (rounds - 1) * (lone_us(N, 0.0) - 2.0) + std::min(tail, part);
+    if (rounds * spread(round) + spread(rest) < whole) return B;
     return part < tail ? rest : 0;
 }
 

@@ -145,7 +145,8 @@ def test_one_tile_row_in_one_launch(route):
     each, not a launch per round."""
     for B in (5000, 20000, 100000, 5000000):
         assert route.count(1, B, CU, CU) <= B % CU
-    assert route.count(1, 512, CU, CU) == 512
+    for B in (512, 1000, 2000):   # measured sooner done round by round
+        assert route.count(1, B, CU, CU) == B
 
 
 def _group(route, sizes):
