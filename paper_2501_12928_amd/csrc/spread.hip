@@ -376,9 +376,12 @@ __device__ __forceinline__ bool last_update(SpreadShared &sh, const double2 *L, 
 
 // PER_CU workgroups of four waves per CU (spread_per_cu). Two: 256 registers a
 // wave, and while one waits for a tile the other computes. One, with
-// last_update: 256 registers as well, although a few spill there (with 512 the
-// accumulators moved between the two register files, 36 us a column against 31).
-template <int PER_CU>
+// last_update: 256 registers as well (with 512 the accumulators move between the
+// two register files, 36 us a column against 31). Neither form spills vector
+// registers. GROUP: task, count and off are there; otherwise one instance, slots of
+// one size and theta in order (as run-time choices they cost one theta at n = 200
+// 95.9 us in place of 95.1).
+template <int PER_CU, bool GROUP>
 __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
     constexpr bool hand = PER_CU == 1;
     __shared__ SpreadShared sh;
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         if (t >= a.units) break;
         int count;
         for (;;) {
-            count = a.count ? uniform(a.count[rem]) : a.ntask;
+            count = GROUP ? uniform(a.count[rem]) : a.ntask;
             if (t < base + (int64_t)count * rem) break;
             base += (int64_t)count * rem;
             --rem;
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         const int u = (int)((t - base) / count), slot = (int)(t - base - (int64_t)u * count);
         int inst = 0;
         int64_t bt = slot;
-        if (a.task) {
+        if constexpr (GROUP) {
             const int2 td = a.task[slot];
             inst = uniform(td.x);
             bt = uniform(td.y);
@@ -415,8 +418,15 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
         const CallDesc C = a.call[inst];
         const int N = uniform(I.N), j = N - rem, i = j + u, stop = a.n_max;
         const double2 *A = uniform_ptr(I.A);
-        const longlong2 off = a.off ? a.off[slot] : make_longlong2(slot * a.slot_elems, slot * a.slot_y);
-        double2 *L = uniform_ptr(a.Lw + off.x), *yv = uniform_ptr(a.yw + off.y);
+        double2 *L, *yv;
+        if constexpr (GROUP) {
+            const longlong2 off = a.off[slot];
+            L = uniform_ptr(a.Lw + off.x);
+            yv = uniform_ptr(a.yw + off.y);
+        } else {
+            L = uniform_ptr(a.Lw + slot * a.slot_elems);
+            yv = uniform_ptr(a.yw + slot * a.slot_y);
+        }
         int32_t *prog = uniform_ptr(a.prog + (int64_t)slot * (a.n_max + SPREAD_EXTRA));
         d4 xr[4], xi[4];
         if (u <= 1) __builtin_amdgcn_s_setprio(2);
@@ -575,10 +585,9 @@ __global__ __launch_bounds__(256, 2) void spread_kernel(SpreadParams a) {
 hipError_t launch_spread(const SpreadParams &p, int num_cu, hipStream_t s) {
     const int64_t grid = std::min<int64_t>(p.units, (int64_t)p.per_cu * num_cu);
     if (grid < 1) return hipSuccess;
-    if (p.per_cu == 1)
-        hipLaunchKernelGGL(spread_kernel<1>, dim3((unsigned)grid), dim3(256), 0, s, p);
-    else
-        hipLaunchKernelGGL(spread_kernel<2>, dim3((unsigned)grid), dim3(256), 0, s, p);
+    const auto kernel = p.off ? (p.per_cu == 1 ? spread_kernel<1, true> : spread_kernel<2, true>)
+                              : (p.per_cu == 1 ? spread_kernel<1, false> : spread_kernel<2, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
