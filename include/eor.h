@@ -177,8 +177,9 @@ eor_status eor_set_workspace_limit(eor_ctx *ctx, size_t bytes);
 
 /*
  * Launch choices of this context's eor_loglike_batch / eor_loglike_terms
- * where a theta has a workgroup of its own (execution parameters only; results do not depend on them beyond the
- * summation order of the tile updates, which is the same for all):
+ * where a theta has a workgroup of its own (execution parameters only; results
+ * do not depend on them beyond the summation order of the tile updates, which is
+ * the same for all):
  *   stages          k-steps of 4 columns the panel update prefetches (2 or 4)
  *   wg_per_cu       theta in flight per compute unit (1 or 2)
  *   tiles_per_pass  1: workgroups of 4 waves; 2: workgroups of 8 waves,
@@ -210,7 +211,8 @@ eor_status eor_get_tile_size(const eor_ctx *ctx, int32_t *ts);
  * resident workgroups takes (instance, theta) tasks, longest first, until all
  * are done, so small and large problems share the GPU without a tail per
  * dataset; with few theta, or a few large ones that would outlast the rest, the
- * tiles of every theta are spread over all workgroups instead.
+ * tiles of every theta are spread over all workgroups instead, if the memory for
+ * that can be had.
  *
  * eor_group_create: n_inst (1..64) contexts on one device, each precomputed
  * before every eor_group_loglike call. The group keeps pointers to the

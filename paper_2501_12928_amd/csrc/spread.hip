@@ -34,18 +34,17 @@
 // Tile (j+1, j) would be formed, announced and read back between the two;
 // instead its unit hands over X (what Linv_jj is still to be applied to) while
 // tile (j, j) is being factored, and the unit of tile (j+1, j+1) forms L_(j+1)j
-// itself and updates from LDS (last_update): 37 -> 31 us per column; Linv_jj is
-// announced by itself, before y_j: 29.5; and a diagonal tile is formed only in
-// its lower triangle (DiagBlocks): 27 us (factor 14.4, stored and announced 2,
-// seen and loaded 2.3, tile below 4.3, update and move to LDS 4). With one
-// workgroup per CU (spread_per_cu) one theta at n = 4096 takes 1.72 ms (253 by
-// one workgroup, 2.46 before these three and with two per CU), at n = 2048 0.85
-// (33.5, 1.12), at n = 200 109 us (190, 134). With many theta
-// the FP64 matrix cores and the panels' traffic (each unit streams both of its
-// panels alone) bound: 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s, against 79
-// with 256 theta of one workgroup each, where two tiles share a panel; so full
-// rounds stay there (spread_count in abi.hip, build_spread in runtime.hip). There
-// nothing is handed over: with it 64 theta at n = 1003 took 1.89 ms, 1.75 without.
+// itself and updates from LDS (last_update); Linv_jj is announced by itself,
+// before y_j; and a diagonal tile is formed only in its lower triangle
+// (DiagBlocks). A column takes 27 us, 37 without the three (factor 14.4, stored and
+// announced 2, seen and loaded 2.3, tile below 4.3, update and move to LDS 4). With
+// one workgroup per CU (spread_per_cu) one theta at n = 4096 takes 1.72 ms (253 by
+// one workgroup of likelihood.hip), at n = 2048 0.85 (33.5), at n = 200 95 us (168).
+// With many theta the FP64 matrix cores and the panels' traffic (each unit streams
+// both of its panels alone) bound: 64 theta at n = 4096 78.5 ms = 74.7 TFLOP/s,
+// against 79 with 256 theta of one workgroup each, where two tiles share a panel;
+// so full rounds stay there (route.h). Nothing is handed over then: with it 64 theta
+// at n = 1003 took 1.89 ms, 1.75 without.
 #include <algorithm>
 
 #include "like_device.h"

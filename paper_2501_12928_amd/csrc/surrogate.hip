@@ -140,15 +140,17 @@ __host__ __device__ inline int64_t share_count(int H, int n_in) { return (int64_
 // B alike, so that each lane loads four consecutive k with one 16-byte read.
 // In the backward pass a step has few workgroups (160 at 512 samples of five
 // members) and each is a chain of two products, two sets of erf and exp and two
-// products back; widths that fill tiles of 256 take sixteen waves, four per
-// SIMD, to cover each other's latencies: 29.6 us a step's first kernel at width
-// 256 where eight took 31.8 (both with guarded loads; 26 now). Staging W2 through LDS, one or four stages ahead,
-// left the two W2 products at 7.6 and 6.9 us each (twice their matrix time), and
-// eight samples' groups in flight in the update made that kernel slower (12.6
-// against 10.7 us), so neither is here. FP32 MFMA and vector instructions of
-// other waves do not overlap on this part: forward only, at a million
-// proposals, the SIMDs are 55% in MFMA and 41% in vector instructions, most of
-// them erf.
+// products back. Widths of an even number of 128-wide tiles (132 to 256, 388 to
+// 512) take sixteen waves, four per SIMD, to cover each other's latencies; an odd
+// number (to 128, 260 to 384) cannot be halved and takes eight. Loss and gradient of
+// five members, sixteen against eight: width 132 at 16, 512 and 2048 samples 18.5 /
+// 20.2, 30.2 / 31.5 and 68.8 / 68.2 us; 256 25.9 / 27.5, 35.9 / 37.7 and 88.7 / 85.5; 512
+// 67.0 / 70.1, 88.3 / 91.2 and 257 / 265. Staging W2 through LDS, one or four stages
+// ahead, left the two W2 products at twice their matrix time, and eight samples'
+// groups in flight made the update slower (12.6 against 10.7 us), so neither is here.
+// FP32 MFMA and vector instructions of other waves do not overlap on this part:
+// forward only, at a million proposals, MFMA takes 58% of the SIMDs' time, most of
+// the rest is vector instructions, the larger part of them erff.
 template <int CT, int NW, int RT, bool BWD>
 __global__ __launch_bounds__(64 * NW) void mlp_kernel(MlpArgs a) {
     static_assert(!BWD || RT == 1, "the backward pass takes 16 samples per workgroup");
@@ -860,7 +862,7 @@ MlpArgs net_args(const eor_surrogate &s) {
 template <int NW, int RT, bool BWD>
 void launch_mlp(const MlpArgs &a, int CT, int members, hipStream_t st) {
     const dim3 grid((unsigned)((a.nb + ST * RT - 1) / (ST * RT)), (unsigned)members), block(64 * NW);
-    if constexpr (NW == 8) {  // widths up to 512 in tiles of 128; whole tiles of 256 by sixteen waves
+    if constexpr (NW == 8) {  // widths up to 512 in tiles of 128, an even number of them by sixteen waves
         switch (CT) {
         case 1: hipLaunchKernelGGL((mlp_kernel<1, NW, RT, BWD>), grid, block, 0, st, a); break;
         case 2: hipLaunchKernelGGL((mlp_kernel<1, 16, RT, BWD>), grid, dim3(1024), 0, st, a); break;

@@ -100,8 +100,8 @@ __device__ inline int real_blocks(int64_t n, int j) {
     return left >= S ? S / 16 : left <= 0 ? 0 : (int)((left + 15) / 16);
 }
 
-// D (S x S, column-major with leading dimension S + 1, both triangles valid)
-// becomes L^{-1} of its Cholesky factor L in its lower 16 x 16 blocks (the
+// D (S x S, column-major with leading dimension S + 1; read are the 16 x 16 blocks
+// of the lower triangle, those on the diagonal in both of theirs) becomes L^{-1} of its Cholesky factor L in its lower 16 x 16 blocks (the
 // blocks on the diagonal with exact zeros above theirs; the blocks above the
 // diagonal hold no result); dg receives the pivots L_cc^2. Called by all NW
 // waves (NW >= S / 16), after a barrier that follows the last write of D.
@@ -123,10 +123,9 @@ __device__ inline int real_blocks(int64_t n, int j) {
 // barriers per block column instead of one per column; the leading dimension
 // S + 1 keeps every operand read free of bank conflicts. Which wave forms a
 // block does not change its bits. At S = 64 with eight waves 12.7 us (30460
-// cycles, of which 4 x 4040 are the eliminations), where one barrier per
-// column and a separate blocked inverse, with the sums of ln d and |y|^2 on
-// one thread, took about 60 us more per tile: one theta at n = 200 444 -> 175
-// us, 256 at n = 2048 40.8 -> 39.3 ms.
+// cycles, of which 4 x 4040 are the eliminations, about 60 instructions a step at
+// four cycles); with one barrier per column and a separate blocked inverse about
+// 60 us more.
 template <int S, int NW>
 __device__ __forceinline__ int tile_factor(double2 *D, double *dg, int *fail_sh, int nb) {
     constexpr int LD = S + 1;
