@@ -208,7 +208,8 @@ __global__ __launch_bounds__(PT) void ooc_potrf_kernel(const double2 *__restrict
     if (st->info != 0) return;
     const int tid = threadIdx.x, wv = uniform(tid >> 6), l16 = tid & 15, q = (tid >> 4) & 3;
     {
-        // the lower triangle, and its conjugate above; all loads in flight together
+        // the lower triangle, in the blocks on the diagonal its conjugate above; all
+        // loads in flight together
         double2 v[OT2 / PT];
 #pragma unroll
         for (int u = 0; u < OT2 / PT; ++u) v[u] = C0[tid + PT * u];
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(PT) void ooc_potrf_kernel(const double2 *__restrict
         for (int u = 0; u < OT2 / PT; ++u) {
             const int e = tid + PT * u, r = e / OT, c = e % OT;
             if (c <= r) D[c * (OT + 1) + r] = v[u];
-            if (c < r) D[r * (OT + 1) + c] = make_double2(v[u].x, -v[u].y);
+            if (c < r && c / 16 == r / 16) D[r * (OT + 1) + c] = make_double2(v[u].x, -v[u].y);
         }
     }
     if (tid < OT) wj[tid] = w[OT * j + tid];
